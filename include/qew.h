@@ -67,7 +67,9 @@ typedef int32_t qew_status;
 #define QEW_FP32_SPLIT 1      /* u = int32 cell + FP32 offset in [0,1); FP64 sums     */
 
 /* kernel path */
-#define QEW_ONE_STEP 0        /* one Euler step per launch, all 4 nodes regenerated    */
+#define QEW_ONE_STEP 0        /* split: one Euler step per launch, all 4 nodes regenerated;
+                                 FP64: up to 112 steps per launch on overlapping tiles
+                                 (geometry from the problem's size), the same results    */
 #define QEW_FUSED    1        /* k Euler steps per launch on register tiles with halos */
 
 /* qew_problem.flags */

@@ -8,6 +8,10 @@
 //   k_step_plain   one FP64 Euler step per launch, one thread per site, four
 //                  Philox nodes regenerated per site update.  HBM traffic is
 //                  16 B per update (read u, write u; neighbours hit L1/L2).
+//   k_blocked_plain, k_lanes
+//                  several FP64 steps per launch on overlapping tiles, nodes
+//                  made when a site enters a cell: wide tiles for large
+//                  problems, narrow ones without a request path for small.
 //   k_step_split1  the same on the split state (int32 cell + FP32 offset).
 //   k_step_fused   `nsub` split Euler steps per launch.  Each workgroup owns
 //                  a tile of 256*P consecutive sites held in registers (P
@@ -23,6 +27,8 @@
 //                  v, ubar, w2.
 #include "qew_device.hpp"
 #include "qew_internal.hpp"
+
+#include <type_traits>
 
 namespace qew {
 
@@ -619,6 +625,603 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
 }
 
 // ---------------------------------------------------------------------------
+// Temporally blocked FP64 kernel: nsub <= halo Euler steps per launch.
+//
+// The one-step kernel makes the four nodes of every site at every step (some
+// 200 vector operations); a site changes its cell only every 20 steps or so.
+// Here a workgroup keeps a tile of T = 256 P consecutive sites (the valid part
+// and `halo` more on each side, recomputed redundantly) in registers with the
+// coefficients of their current cells, and makes one node when a site enters a
+// new cell.  The request path is that of k_step_fused: sites that changed cell
+// post a request in LDS, the same wave serves them one per lane and the
+// requesters read their new coefficients back.
+//
+// Bound by VALU issue: 16 FP64 operations of 4 cycles per site and step (some
+// 10 us per step at 2^22 x 4), 6 to post a site's cell change, and a service
+// pass of some 90 instructions per wave and sub-step, whose 64 lanes about 22
+// requests of a wave's 512 sites fill to a third.  2048-site tiles at k = 64:
+// 25.3 us per step against 97 of the one-step kernel (3072-site tiles 28.0,
+// 1024-site 29.2: registers and LDS for fewer waves, the pass shared by fewer
+// sites); a launch costs 110 us more for loads and the nodes of its tiles.
+// Random bond, whose windows take twice the LDS, on 1024-site tiles: 42
+// against 406 us.
+//
+// Same results as the one-step kernel, bit for bit: the coefficients are the
+// sums of spline_f64 (halved, which is exact), the steps its operations in its
+// order.
+// ---------------------------------------------------------------------------
+// Coefficients of F_p in the offset s of a cell with (scaled) nodes p0..p3:
+// a0 + s (a1 + s (a2 + s a3)) rounds as spline_f64 does.
+template <int KIND>
+struct CoefD {
+  static constexpr int N = KIND == kRF ? 4 : (KIND == kRB ? 3 : 1);
+  double a[N];
+};
+
+template <int KIND>
+__device__ __forceinline__ CoefD<KIND> coef_f64(double p0, double p1, double p2, double p3) {
+  CoefD<KIND> c;
+  if constexpr (KIND == kRBLin) {
+    c.a[0] = -(p2 - p1);
+  } else if constexpr (KIND == kRFPc) {
+    c.a[0] = p1;
+  } else {
+    const double c1 = p2 - p0;
+    const double c2 = 2.0 * p0 - 5.0 * p1 + 4.0 * p2 - p3;
+    const double c3 = -p0 + 3.0 * p1 - 3.0 * p2 + p3;
+    if constexpr (KIND == kRF) {
+      c.a[0] = p1;
+      c.a[1] = 0.5 * c1;
+      c.a[2] = 0.5 * c2;
+      c.a[3] = 0.5 * c3;
+    } else {
+      c.a[0] = -0.5 * c1;
+      c.a[1] = -c2;
+      c.a[2] = -0.5 * (3.0 * c3);
+    }
+  }
+  return c;
+}
+
+template <int KIND>
+__device__ __forceinline__ double pin_f64(const CoefD<KIND>& c, double s) {
+  if constexpr (KIND == kRF) return c.a[0] + s * (c.a[1] + s * (c.a[2] + s * c.a[3]));
+  else if constexpr (KIND == kRB) return c.a[0] + s * (c.a[1] + s * c.a[2]);
+  else return c.a[0];
+}
+
+// Unscaled nodes kept for a site of cell n, nodes n + kLow .. n + kHigh (the
+// random-field values are exact in FP32).
+template <int KIND>
+struct WindowD {
+  static constexpr int kLow = (KIND == kRF || KIND == kRB) ? -1 : 0;
+  static constexpr int kHigh = (KIND == kRF || KIND == kRB) ? 2 : (KIND == kRBLin ? 1 : 0);
+  static constexpr int kCount = kHigh - kLow + 1;
+  using type = std::conditional_t<KIND == kRF, float, double>;
+  type v[kCount];
+  __device__ __forceinline__ void push_up(double x) {
+#pragma unroll
+    for (int i = 0; i + 1 < kCount; ++i) v[i] = v[i + 1];
+    v[kCount - 1] = (type)x;
+  }
+  __device__ __forceinline__ void push_down(double x) {
+#pragma unroll
+    for (int i = kCount - 1; i > 0; --i) v[i] = v[i - 1];
+    v[0] = (type)x;
+  }
+  __device__ __forceinline__ CoefD<KIND> coef(double strength, bool unit) const {
+    if constexpr (KIND == kRF) {
+      if (unit) {
+        // Unit strength: the nodes are multiples of 2^-24 below 1, every sum of
+        // coef_f64 is exact, and so is this shorter form of it.
+        const double q0 = v[0], q1 = v[1], q2 = v[2], q3 = v[3];
+        CoefD<KIND> c;
+        c.a[0] = q1;
+        c.a[1] = 0.5 * (q2 - q0);
+        c.a[2] = fma(-0.5, q3, fma(2.0, q2, fma(-2.5, q1, q0)));
+        c.a[3] = fma(1.5, q1 - q2, 0.5 * (q3 - q0));
+        return c;
+      }
+    }
+    double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) p[i + 1 + kLow] = strength * (double)v[i];
+    return coef_f64<KIND>(p[0], p[1], p[2], p[3]);
+  }
+};
+
+__device__ __forceinline__ double from_lower_lane(double x) {
+  const uint64_t v = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x138, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, true);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double from_upper_lane(double x) {
+  const uint64_t v = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x130, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x130, 0xF, 0xF, true);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Waves per SIMD the register allocation must allow (the Box-Muller transform
+// of the Gaussian kinds needs more registers).
+constexpr int blocked_min_waves(int kind) { return kind == kRF || kind == kRB ? 3 : 2; }
+
+template <int KIND, int P>
+__global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
+    k_blocked_plain(Tables t, const double* __restrict__ uin, double* __restrict__ uout, Phys ph, int halo,
+                    int nsub) {
+  constexpr int T = kBlock * P;
+  constexpr int NW = kBlock / 64;
+  constexpr int RQ = kReqPerWave;
+  constexpr int NC = CoefD<KIND>::N;
+  using Win = WindowD<KIND>;
+  // A request: the new cell and the site's index; its reply: the coefficients.
+  struct __align__(16) Req {
+    double cell;
+    int site, pad;
+    double more[2];
+  };
+  __shared__ __align__(16) Win s_win[T];  // nodes of the site's cell, slot-major
+  __shared__ int s_cell[T];
+  __shared__ Req s_req[NW * (RQ + 1)];     // per wave: RQ requests, then one sink slot
+  __shared__ double s_edge[2][NW + 2][2];  // end sites of each wave, double-buffered
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = uniform_i32(tid >> 6);
+  const double cel = ph.c, dt = ph.dt, str = ph.strength;
+  const bool unit = str == 1.0;
+  const int s = uniform_i32(t.ft_s[blockIdx.x]);
+  const int p0 = uniform_i32(t.ft_p0[blockIdx.x]);
+  const int len = uniform_i32(t.ft_len[blockIdx.x]);
+  const int L = uniform_i32(t.L[s]);
+  const int64_t base = uniform_i64(t.off[s]);
+  const uint32_t id = (uint32_t)uniform_i32((int)t.did[s]);
+  const double f = t.f[s];
+  const int start = p0 - halo;
+  int start_mod = start % L;
+  if (start_mod < 0) start_mod += L;
+  // Column of tile-local position lp (wrapped only in tiles that cross their chain's end).
+  const bool wraps = start_mod + T > L;
+  auto column = [&](int lp) -> int {
+    int j = start_mod + lp;
+    if (wraps) {
+      if (j >= L) j -= L;
+      if (j >= L) j %= L;
+    }
+    return j;
+  };
+  // The window of a site of column j that moved by `move` cells to cell n (one
+  // node; all of them after a jump or at the start, move = 0).
+  auto advance_window = [&](Win& w, int j, int32_t n, int move) {
+    if (__all(move == 1)) {  // the usual case: every site of the wave moved forward by one
+      w.push_up(node_f64<KIND>((uint32_t)j, n + Win::kHigh, id, ph.k0, ph.k1, ph.period));
+      return;
+    }
+    const bool down = move == -1;
+    int32_t m = move == 1 ? n + Win::kHigh : n + Win::kLow;
+    const int last = down ? m : n + Win::kHigh;
+#pragma unroll 1
+    for (; m <= last; ++m) {
+      const double x = node_f64<KIND>((uint32_t)j, m, id, ph.k0, ph.k1, ph.period);
+      if (down) w.push_down(x);
+      else w.push_up(x);
+    }
+  };
+
+  double u[P], nf[P];
+  CoefD<KIND> a[P];
+  {
+    const int j = column(tid * P);
+    if ((P % 2) == 0 && start >= 0 && start + T <= L && (start & 1) == 0) {
+      const double2* src = reinterpret_cast<const double2*>(uin + base + start + tid * P);
+#pragma unroll
+      for (int i = 0; i < P / 2; ++i) {
+        const double2 x = src[i];
+        u[2 * i] = x.x;
+        u[2 * i + 1] = x.y;
+      }
+    } else {
+      int jj = j;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        u[i] = uin[base + jj];
+        jj = (jj + 1 == L) ? 0 : jj + 1;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      nf[i] = floor(u[i]);
+      s_cell[i * kBlock + tid] = (int32_t)nf[i];
+    }
+    int jj = j;
+#pragma unroll 1
+    for (int i = 0; i < P; ++i) {
+      Win w{};
+      advance_window(w, jj, s_cell[i * kBlock + tid], 0);
+      s_win[i * kBlock + tid] = w;
+      jj = (jj + 1 == L) ? 0 : jj + 1;
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) a[i] = s_win[i * kBlock + tid].coef(str, unit);
+  }
+  if (lane == 0) s_edge[0][wv + 1][0] = u[0];
+  if (lane == 63) s_edge[0][wv + 1][1] = u[P - 1];
+  __syncthreads();
+
+  const uint32_t rbase_b = (uint32_t)(wv * (RQ + 1)) * (uint32_t)sizeof(Req);
+  const uint32_t sink_b = rbase_b + (uint32_t)RQ * (uint32_t)sizeof(Req);
+  for (int sub = 0; sub < nsub; ++sub) {
+    const int par = sub & 1;
+    // Neighbours of this thread's end sites.  The tile ends reflect.
+    double ul = from_lower_lane(u[P - 1]);
+    double ur = from_upper_lane(u[0]);
+    if (lane == 0) ul = wv > 0 ? s_edge[par][wv][1] : u[0];
+    if (lane == 63) ur = wv < NW - 1 ? s_edge[par][wv + 2][0] : u[P - 1];
+
+    __builtin_amdgcn_s_setprio(3);
+    bool mv[P];
+    uint64_t moved[P];
+    uint64_t any_moved = 0u;
+    double pl = ul;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const double nr = (i + 1 < P) ? u[i + 1] : ur;
+      const double lap = fma(-2.0, u[i], nr + pl);  // 2 u is exact: one rounding, as (nr + pl) - 2 u
+      const double F = ((cel * lap) + f) + pin_f64<KIND>(a[i], u[i] - nf[i]);
+      pl = u[i];
+      u[i] = u[i] + dt * F;
+      const double fl = floor(u[i]);
+      mv[i] = fl != nf[i];
+      moved[i] = __ballot(mv[i]);
+      any_moved |= moved[i];
+      nf[i] = fl;
+    }
+    if (any_moved != 0u) {
+      uint32_t kb[P];
+      uint32_t nreq = 0u;  // wave-uniform
+      // Requests past the region land in its sink slot; they come in later rounds.
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        kb[i] = min(mbcnt64(moved[i]) * (uint32_t)sizeof(Req) +
+                        (uint32_t)uniform_i32((int)(rbase_b + nreq * (uint32_t)sizeof(Req))),
+                    sink_b);
+        if (mv[i]) {
+          Req* rq = reinterpret_cast<Req*>(reinterpret_cast<char*>(s_req) + kb[i]);
+          rq->cell = nf[i];
+          rq->site = i * kBlock + tid;
+        }
+        nreq += (uint32_t)__popcll(moved[i]);
+      }
+      __builtin_amdgcn_s_setprio(0);
+      // Lane q serves request q of this wave; a wave's LDS operations complete in order.
+      auto serve = [&](uint32_t count) {
+        __builtin_amdgcn_wave_barrier();
+        if ((uint32_t)lane < count) {
+          Req* rq = &s_req[wv * (RQ + 1) + lane];
+          const int ni = rq->site;
+          const int32_t n = (int32_t)rq->cell;
+          Win w = s_win[ni];
+          advance_window(w, column((int)(((uint32_t)ni % kBlock) * P + (uint32_t)ni / kBlock)), n, n - s_cell[ni]);
+          s_win[ni] = w;
+          s_cell[ni] = n;
+          const CoefD<KIND> c = w.coef(str, unit);
+          double* reply = reinterpret_cast<double*>(rq);
+#pragma unroll
+          for (int q = 0; q < NC; ++q) reply[q] = c.a[q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      };
+      auto read_back = [&](int i, uint32_t at) {
+        const double* reply = reinterpret_cast<const double*>(reinterpret_cast<const char*>(s_req) + at);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) a[i].a[q] = reply[q];
+      };
+      serve(nreq < (uint32_t)RQ ? nreq : (uint32_t)RQ);
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (mv[i]) read_back(i, kb[i]);
+      __builtin_amdgcn_wave_barrier();
+      // A burst of more cell changes than the region holds: further rounds.
+      for (uint32_t done = RQ; done < nreq; done += RQ) {
+        uint32_t first = 0u;
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          const uint32_t r = first + mbcnt64(moved[i]) - done;
+          kb[i] = rbase_b + r * (uint32_t)sizeof(Req);
+          if (mv[i] && r < (uint32_t)RQ) {
+            Req* rq = reinterpret_cast<Req*>(reinterpret_cast<char*>(s_req) + kb[i]);
+            rq->cell = nf[i];
+            rq->site = i * kBlock + tid;
+          }
+          first += (uint32_t)__popcll(moved[i]);
+        }
+        serve(nreq - done < (uint32_t)RQ ? nreq - done : (uint32_t)RQ);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+          if (mv[i] && kb[i] - rbase_b < (uint32_t)(RQ * sizeof(Req))) read_back(i, kb[i]);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __builtin_amdgcn_s_setprio(2);
+    if (lane == 0) s_edge[par ^ 1][wv + 1][0] = u[0];
+    if (lane == 63) s_edge[par ^ 1][wv + 1][1] = u[P - 1];
+    __syncthreads();
+  }
+
+  // Write the valid part: tile-local q in [halo, halo + len).
+  const int q0 = tid * P;
+  double* dst = uout + base + p0 - halo + q0;
+  if ((P % 2) == 0 && q0 >= halo && q0 + P <= halo + len && ((p0 - halo) & 1) == 0) {
+#pragma unroll
+    for (int i = 0; i < P / 2; ++i) reinterpret_cast<double2*>(dst)[i] = make_double2(u[2 * i], u[2 * i + 1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      if (q0 + i >= halo && q0 + i < halo + len) dst[i] = u[i];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Temporally blocked kernel for small problems, both precisions: nsub <= halo
+// Euler steps per launch on tiles of 256 P sites with P = 1, 2 or 4.
+//
+// When there are only a few sites per CU, a sub-step costs what its longest
+// dependent chain costs.  The request path of the wide-tile kernels (post in
+// LDS, serve, read back) is such a chain, some 1300 cycles, so here every lane
+// serves its own sites: the window of the current cell and the node after it
+// stay in registers, up to kSpare nodes further ahead in LDS.  A site that
+// enters the next cell only forms its coefficients.  When a lane has no node
+// left, the whole wave makes one node ahead for every lane with room, in one
+// pass of the generator.  The edges are published before that work, so the
+// barrier finds them written.  FP64, four chains of 1024 sites: 0.37 us per
+// step on 256-site tiles (the request path on them: 1.04, one step per launch:
+// 4.1), of which 0.2 us are the steps, the edges and the barrier.
+// ---------------------------------------------------------------------------
+constexpr int kSpare = 4;
+
+template <int KIND>
+struct LanesD {  // FP64 state
+  using Buf = const double*;
+  using Out = double*;
+  using node_t = typename WindowD<KIND>::type;
+  using edge_t = double;
+  static constexpr int kHigh = WindowD<KIND>::kHigh;
+  struct Consts {
+    double c, dt, str, f;
+    bool unit;
+  };
+  static __device__ __forceinline__ Consts consts(const Phys& ph, const Tables& t, int s) {
+    return {ph.c, ph.dt, ph.strength, t.f[s], ph.strength == 1.0};
+  }
+  static __device__ __forceinline__ int32_t cell_base(Buf, int64_t) { return 0; }
+  struct Site {
+    double u, nf;
+    CoefD<KIND> a;
+    WindowD<KIND> w;
+  };
+  static __device__ __forceinline__ bool load(Buf in, int64_t g, int32_t, Site& x) {
+    x.u = in[g];
+    x.nf = floor(x.u);
+    return false;
+  }
+  static __device__ __forceinline__ int32_t cell(const Site& x, int32_t) { return (int32_t)x.nf; }
+  static __device__ __forceinline__ edge_t edge(const Site& x) { return x.u; }
+  static __device__ __forceinline__ edge_t lower(const edge_t& e) { return from_lower_lane(e); }
+  static __device__ __forceinline__ edge_t upper(const edge_t& e) { return from_upper_lane(e); }
+  static constexpr bool kWindowInHbm = false;
+  static __device__ __forceinline__ void load_window(Buf, int64_t, Site&) {}
+  static __device__ __forceinline__ node_t node(uint32_t j, int32_t n, uint32_t id, const Phys& ph) {
+    return (node_t)node_f64<KIND>(j, n, id, ph.k0, ph.k1, ph.period);
+  }
+  static __device__ __forceinline__ void coef(Site& x, const Consts& k) { x.a = x.w.coef(k.str, k.unit); }
+  // One step with the old values of the neighbours; returns the cells moved.
+  static __device__ __forceinline__ double step(Site& x, edge_t l, edge_t r, const Consts& k) {
+    const double lap = fma(-2.0, x.u, r + l);  // 2 u is exact: one rounding, as (r + l) - 2 u
+    const double F = ((k.c * lap) + k.f) + pin_f64<KIND>(x.a, x.u - x.nf);
+    x.u = x.u + k.dt * F;
+    const double fl = floor(x.u);
+    const double d = fl - x.nf;
+    x.nf = fl;
+    return d;
+  }
+  static __device__ __forceinline__ void store(Out out, int64_t g, const Site& x, int32_t) { out[g] = x.u; }
+};
+
+template <int KIND>
+struct LanesS {  // split state; the window comes from and returns to the node cache in HBM
+  using Buf = SplitBuf;
+  using Out = SplitBuf;
+  using node_t = float;
+  static constexpr int kHigh = 2;
+  struct edge_t {
+    float c, r;
+  };
+  struct Consts {
+    float c, dt, g, f;
+  };
+  static __device__ __forceinline__ Consts consts(const Phys& ph, const Tables& t, int s) {
+    return {ph.cf, ph.dtf, ph.sgn_strf, t.f32[s]};
+  }
+  static __device__ __forceinline__ int32_t cell_base(const Buf& in, int64_t g) { return uniform_i32(in.cell[g]); }
+  struct Window {
+    float v[4];
+    __device__ __forceinline__ void push_up(float x) {
+      v[0] = v[1];
+      v[1] = v[2];
+      v[2] = v[3];
+      v[3] = x;
+    }
+  };
+  struct Site {
+    float c, r;  // cell relative to the tile's first (an exact integer), offset
+    float4 a;
+    Window w;
+  };
+  static __device__ __forceinline__ bool load(const Buf& in, int64_t g, int32_t cbase, Site& x) {
+    const int32_t d = in.cell[g] - cbase;
+    x.c = (float)d;
+    x.r = in.frac[g];
+    return (uint32_t)(d + (1 << 23)) >= (1u << 24);  // the difference must be exact in FP32
+  }
+  static __device__ __forceinline__ int32_t cell(const Site& x, int32_t cbase) { return cbase + (int32_t)x.c; }
+  static __device__ __forceinline__ edge_t edge(const Site& x) { return {x.c, x.r}; }
+  static __device__ __forceinline__ edge_t lower(const edge_t& e) { return {from_lower_lane(e.c), from_lower_lane(e.r)}; }
+  static __device__ __forceinline__ edge_t upper(const edge_t& e) { return {from_upper_lane(e.c), from_upper_lane(e.r)}; }
+  static constexpr bool kWindowInHbm = true;
+  static __device__ __forceinline__ void load_window(const Buf& in, int64_t g, Site& x) {
+    const float4 nd = in.nodes[g];
+    x.w.v[0] = nd.x;
+    x.w.v[1] = nd.y;
+    x.w.v[2] = nd.z;
+    x.w.v[3] = nd.w;
+  }
+  static __device__ __forceinline__ node_t node(uint32_t j, int32_t n, uint32_t id, const Phys& ph) {
+    return node_f32<KIND>(j, n, id, ph.k0, ph.k1, ph.period);
+  }
+  static __device__ __forceinline__ void coef(Site& x, const Consts& k) {
+    x.a = spline_coef<KIND>(x.w.v[0], x.w.v[1], x.w.v[2], x.w.v[3], k.g, k.f);
+  }
+  static __device__ __forceinline__ float step(Site& x, edge_t l, edge_t r, const Consts& k) {
+    const float lap = ((r.c - x.c) - (x.c - l.c)) + fmaf(-2.0f, x.r, l.r + r.r);
+    const float F = fmaf(k.c, lap, spline_eval<KIND>(x.a, x.r));
+    const float d = split_advance(x.r, F, k.dt);
+    x.c += d;
+    return d;
+  }
+  static __device__ __forceinline__ void store(const Out& out, int64_t g, const Site& x, int32_t cbase) {
+    out.cell[g] = cbase + (int32_t)x.c;
+    out.frac[g] = x.r;
+    out.nodes[g] = make_float4(x.w.v[0], x.w.v[1], x.w.v[2], x.w.v[3]);
+  }
+};
+
+template <class A, int P>
+__global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
+    k_lanes(Tables t, typename A::Buf in, typename A::Out out, Phys ph, int halo, int nsub) {
+  constexpr int T = kBlock * P;
+  constexpr int NW = kBlock / 64;
+  using node_t = typename A::node_t;
+  using edge_t = typename A::edge_t;
+  __shared__ node_t s_ahead[kSpare][T];    // node m of a site in row m mod kSpare
+  __shared__ edge_t s_edge[2][NW + 2][2];  // end sites of each wave, double-buffered
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = uniform_i32(tid >> 6);
+  const int s = uniform_i32(t.ft_s[blockIdx.x]);
+  const int p0 = uniform_i32(t.ft_p0[blockIdx.x]);
+  const int len = uniform_i32(t.ft_len[blockIdx.x]);
+  const int L = uniform_i32(t.L[s]);
+  const int64_t base = uniform_i64(t.off[s]);
+  const uint32_t id = (uint32_t)uniform_i32((int)t.did[s]);
+  const typename A::Consts k = A::consts(ph, t, s);
+  int start_mod = (p0 - halo) % L;
+  if (start_mod < 0) start_mod += L;
+  const int32_t cbase = A::cell_base(in, base + start_mod);
+
+  typename A::Site x[P];
+  int col[P];        // columns of this thread's sites
+  node_t next[P];    // the node after the window, valid while ahead > 0
+  int ahead[P];      // nodes made beyond the window, at most kSpare
+  bool far = false;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    col[i] = (start_mod + tid * P + i) % L;
+    far |= A::load(in, base + col[i], cbase, x[i]);
+    A::load_window(in, base + col[i], x[i]);
+    next[i] = (node_t)0;
+    ahead[i] = 0;
+  }
+  if (__ballot(far) && lane == 0) atomicOr(t.err, 1);
+  // The whole window of cell n, made anew.
+  auto fresh = [&](typename A::Site& y, int j) {
+    const int32_t n = A::cell(y, cbase);
+#pragma unroll 1
+    for (int m = n + A::kHigh - (int)(sizeof(y.w.v) / sizeof(y.w.v[0])) + 1; m <= n + A::kHigh; ++m)
+      y.w.push_up(A::node((uint32_t)j, m, id, ph));
+  };
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    if constexpr (!A::kWindowInHbm) fresh(x[i], col[i]);
+    A::coef(x[i], k);
+  }
+  // Lanes 0 and 63 publish their wave's ends and read its neighbours' ends, one
+  // LDS access each.  Beyond the tile's ends stand their first values: what
+  // that spoils stays within nsub sites of the end.
+  const bool end_lane = lane == 0 || lane == 63;
+  edge_t* const mine = &s_edge[0][wv + 1][lane == 63 ? 1 : 0];
+  const edge_t* const theirs = lane == 63 ? &s_edge[0][wv + 2][0] : &s_edge[0][wv][1];
+  constexpr int kOther = (NW + 2) * 2;  // from one buffer of s_edge to the other
+  if (end_lane) *mine = A::edge(lane == 63 ? x[P - 1] : x[0]);
+  if (tid == 0) s_edge[0][0][1] = s_edge[1][0][1] = A::edge(x[0]);
+  if (tid == kBlock - 1) s_edge[0][NW + 1][0] = s_edge[1][NW + 1][0] = A::edge(x[P - 1]);
+  __syncthreads();
+
+  auto substep = [&](const int par) __attribute__((always_inline)) {
+    // Neighbours of this thread's end sites.
+    const edge_t across = theirs[par * kOther];
+    edge_t el = A::lower(A::edge(x[P - 1])), er = A::upper(A::edge(x[0]));
+    el = lane == 0 ? across : el;
+    er = lane == 63 ? across : er;
+    decltype(A::step(x[0], el, er, k)) d[P];  // cells moved
+    edge_t prev = el;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const edge_t nb = (i + 1 < P) ? A::edge(x[i + 1 < P ? i + 1 : i]) : er;
+      const edge_t old = A::edge(x[i]);
+      d[i] = A::step(x[i], prev, nb, k);
+      prev = old;
+    }
+    if (end_lane) mine[(par ^ 1) * kOther] = A::edge(lane == 63 ? x[P - 1] : x[0]);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (!__any(d[i] != 0)) continue;
+      const bool up = d[i] == 1;
+      if (__any(up && ahead[i] == 0)) {
+        if (ahead[i] < kSpare) {
+          const int32_t m = A::cell(x[i], cbase) - (up ? 1 : 0) + A::kHigh + 1 + ahead[i];
+          const node_t nd = A::node((uint32_t)col[i], m, id, ph);
+          s_ahead[m & (kSpare - 1)][i * kBlock + tid] = nd;
+          if (ahead[i] == 0) next[i] = nd;
+          ahead[i] += 1;
+        }
+      }
+      if (up) {
+        x[i].w.push_up(next[i]);
+        A::coef(x[i], k);
+        ahead[i] -= 1;
+        next[i] = s_ahead[(A::cell(x[i], cbase) + A::kHigh + 1) & (kSpare - 1)][i * kBlock + tid];
+      }
+      const bool other = d[i] != 0 && !up;
+      if (__any(other)) {  // rare: backwards, or more than one cell
+        if (other) {
+          fresh(x[i], col[i]);
+          A::coef(x[i], k);
+          ahead[i] = 0;
+        }
+      }
+    }
+    __syncthreads();
+  };
+  int sub = 0;
+  for (; sub + 2 <= nsub; sub += 2) {
+    substep(0);
+    substep(1);
+  }
+  if (sub < nsub) substep(0);
+
+  // Write the valid part: tile-local q in [halo, halo + len).
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const int q = tid * P + i;
+    if (q >= halo && q < halo + len) A::store(out, base + p0 - halo + q, x[i], cbase);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Measurement partials (Eqs. (3)-(5)) of the state at one step.
 // ---------------------------------------------------------------------------
 template <int KIND>
@@ -882,6 +1485,27 @@ hipError_t launch_step_plain(const Tables& t, const double* uin, double* uout, c
     case kRB: launch_plain_kind<kRB>(t, uin, uout, ph, part, st); break;
     case kRBLin: launch_plain_kind<kRBLin>(t, uin, uout, ph, part, st); break;
     default: launch_plain_kind<kRFPc>(t, uin, uout, ph, part, st); break;
+  }
+  return hipGetLastError();
+}
+
+template <int KIND>
+static void launch_blocked_kind(const Tables& t, const double* uin, double* uout, const Phys& ph, int tile,
+                                int halo, int nsub, hipStream_t st) {
+  const dim3 g(t.n_ft), b(kBlock);
+  constexpr int wide = KIND == kRB ? 4 : 8;
+  if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 1>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  else if (tile == 512) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  else hipLaunchKernelGGL((k_blocked_plain<KIND, wide>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+}
+
+hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout, const Phys& ph, int kind,
+                                int tile, int halo, int nsub, hipStream_t st) {
+  switch (kind) {
+    case kRF: launch_blocked_kind<kRF>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    case kRB: launch_blocked_kind<kRB>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    case kRBLin: launch_blocked_kind<kRBLin>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    default: launch_blocked_kind<kRFPc>(t, uin, uout, ph, tile, halo, nsub, st); break;
   }
   return hipGetLastError();
 }

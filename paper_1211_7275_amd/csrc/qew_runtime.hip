@@ -79,6 +79,7 @@ struct Layout {
       sq_chunk_first;
   size_t tables_end;
   size_t part, series, ens;
+  size_t bt_s, bt_p0, bt_len, bt_end;  // tiles of the blocked FP64 kernel (always in the workspace)
   size_t small_end;  // end of the tables, partials and series (the regions qew_run_noalloc keeps in scratch)
   size_t sq_series, sq_part, fftA, fftB, stA0, stA1, stB0, stB1, ndA, ndB;
   size_t total;
@@ -117,7 +118,9 @@ struct qew_plan_s {
   std::vector<int32_t> ft_s, ft_p0, ft_len;
   int32_t ft_capacity = 0;
   int32_t k = 1, tile = 0, autotuned = 0;
+  int32_t bk = 0, btile = 0;  // FP64 path: steps per blocked launch (0: one-step launches only) and its tile
   Layout lay{};
+  std::vector<int32_t> bt_img;  // host image of the blocked tiles: samples, first sites, lengths
   std::vector<char> table_img;  // host image of the table region (current tile lists)
   // run state
   char* small_base = nullptr;  // during qew_run_noalloc: base of the small regions (the scratch array)
@@ -144,6 +147,7 @@ namespace {
 bool fused(const qew_plan_t* p) { return p->path == QEW_FUSED; }
 
 void refresh_table_image(qew_plan_t* p);
+int64_t fused_tile_count(const qew_plan_t* p, int tile, int k);
 
 void build_fused_tiles(qew_plan_t* p, int tile, int k) {
   p->ft_s.clear();
@@ -161,6 +165,44 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
   p->k = k;
   p->tile = tile;
   if (p->lay.total) refresh_table_image(p);
+}
+
+// Geometry of the blocked FP64 kernels (none without disorder: a pure stencil
+// runs at the memory's rate one step at a time).  The candidates are tried in
+// order, each taken if it needs at most `most` workgroups.  Measured, us per
+// step (RF, four chains of L):
+//                      256/112  256/96  256/64  512/64  2048/64
+//   L = 2^10             0.37     0.37    0.40    0.62
+//   L = 2^14             0.98     0.63    0.47    0.63
+//   L = 2^16             3.2      1.7     1.05    0.91
+//   L = 2^18                      6.3     3.3     2.34    2.39
+//   L = 2^22                                              25.3   (one step per launch: 97)
+void build_blocked_tiles(qew_plan_t* p) {
+  if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
+  struct { int tile, k; int64_t most; } const geometry[] = {
+      {256, 112, 256}, {256, 96, 256}, {256, 64, 1024}, {512, 64, 2048}, {blocked_wide_tile(p->kind), 64, INT64_MAX}};
+  if (fused_tile_count(p, 256, 112) > INT32_MAX / 2 &&
+      fused_tile_count(p, geometry[4].tile, geometry[4].k) > INT32_MAX / 2)
+    return;
+  int tile = 0;
+  for (const auto& g : geometry) {
+    tile = g.tile;
+    p->bk = g.k;
+    if (fused_tile_count(p, g.tile, g.k) <= g.most) break;
+  }
+  p->btile = tile;
+  const int64_t V = tile - 2 * p->bk;
+  p->ft_s.clear();
+  p->ft_p0.clear();
+  p->ft_len.clear();
+  for (int32_t s = 0; s < p->S; ++s) {
+    const int64_t L = p->L[s];
+    for (int64_t p0 = 0; p0 < L; p0 += V) {
+      p->ft_s.push_back(s);
+      p->ft_p0.push_back((int32_t)p0);
+      p->ft_len.push_back((int32_t)std::min<int64_t>(V, L - p0));
+    }
+  }
 }
 
 int64_t fused_tile_count(const qew_plan_t* p, int tile, int k) {
@@ -191,9 +233,9 @@ void compute_layout(qew_plan_t* p) {
   l.mt_p0 = take(nmt * 4);
   l.mt_len = take(nmt * 4);
   l.mt_first = take((S + 1) * 4);
-  l.ft_s = take(nft * 4);
-  l.ft_p0 = take(nft * 4);
-  l.ft_len = take(nft * 4);
+  l.ft_s = take(fused(p) ? nft * 4 : 0);
+  l.ft_p0 = take(fused(p) ? nft * 4 : 0);
+  l.ft_len = take(fused(p) ? nft * 4 : 0);
   l.sq_chunk_lo = take(p->sq_chunk_lo.size() * 4);
   l.sq_chunk_first = take(p->sq_chunk_first.size() * 4);
   l.tables_end = o;
@@ -201,6 +243,11 @@ void compute_layout(qew_plan_t* p) {
   l.series = take(S * std::max<size_t>(p->meas.size(), 1) * 3 * 8);
   l.ens = take(7 * std::max<size_t>(p->meas.size(), 1) * 8);
   l.small_end = o;
+  const size_t nbt = p->bk ? p->ft_s.size() : 0;
+  l.bt_s = take(nbt * 4);
+  l.bt_p0 = take(nbt * 4);
+  l.bt_len = take(nbt * 4);
+  l.bt_end = o;
   if (p->sq_bins > 0) {
     const size_t half = (size_t)(p->L[0] / 2);
     l.sq_series = take(std::max<size_t>(p->meas.size(), 1) * p->sq_bins * 8);
@@ -251,9 +298,10 @@ Tables tables_of(const qew_plan_t* p, void* ws) {
   t.mt_p0 = reinterpret_cast<const int32_t*>(b + l.mt_p0);
   t.mt_len = reinterpret_cast<const int32_t*>(b + l.mt_len);
   t.mt_first = reinterpret_cast<const int32_t*>(b + l.mt_first);
-  t.ft_s = reinterpret_cast<const int32_t*>(b + l.ft_s);
-  t.ft_p0 = reinterpret_cast<const int32_t*>(b + l.ft_p0);
-  t.ft_len = reinterpret_cast<const int32_t*>(b + l.ft_len);
+  char* w = static_cast<char*>(ws);
+  t.ft_s = reinterpret_cast<const int32_t*>(fused(p) ? b + l.ft_s : w + l.bt_s);
+  t.ft_p0 = reinterpret_cast<const int32_t*>(fused(p) ? b + l.ft_p0 : w + l.bt_p0);
+  t.ft_len = reinterpret_cast<const int32_t*>(fused(p) ? b + l.ft_len : w + l.bt_len);
   t.n_mt = (int32_t)p->mt_s.size();
   t.n_ft = (int32_t)p->ft_s.size();
   t.err = reinterpret_cast<int*>(b + l.err);
@@ -313,9 +361,16 @@ void refresh_table_image(qew_plan_t* p) {
   put(l.mt_p0, p->mt_p0.data(), p->mt_p0.size() * 4);
   put(l.mt_len, p->mt_len.data(), p->mt_len.size() * 4);
   put(l.mt_first, p->mt_first.data(), p->mt_first.size() * 4);
-  put(l.ft_s, p->ft_s.data(), p->ft_s.size() * 4);
-  put(l.ft_p0, p->ft_p0.data(), p->ft_p0.size() * 4);
-  put(l.ft_len, p->ft_len.data(), p->ft_len.size() * 4);
+  if (fused(p)) {
+    put(l.ft_s, p->ft_s.data(), p->ft_s.size() * 4);
+    put(l.ft_p0, p->ft_p0.data(), p->ft_p0.size() * 4);
+    put(l.ft_len, p->ft_len.data(), p->ft_len.size() * 4);
+  } else if (p->bk) {
+    p->bt_img.assign((l.bt_end - l.bt_s) / 4, 0);
+    std::copy(p->ft_s.begin(), p->ft_s.end(), p->bt_img.begin());
+    std::copy(p->ft_p0.begin(), p->ft_p0.end(), p->bt_img.begin() + (l.bt_p0 - l.bt_s) / 4);
+    std::copy(p->ft_len.begin(), p->ft_len.end(), p->bt_img.begin() + (l.bt_len - l.bt_s) / 4);
+  }
   put(l.sq_chunk_lo, p->sq_chunk_lo.data(), p->sq_chunk_lo.size() * 4);
   put(l.sq_chunk_first, p->sq_chunk_first.data(), p->sq_chunk_first.size() * 4);
 }
@@ -323,6 +378,9 @@ void refresh_table_image(qew_plan_t* p) {
 // Copy the plan's table image to the small regions' base (no allocation).
 qew_status upload_tables(qew_plan_t* p, void* ws, hipStream_t st) {
   QEW_HIP(hipMemcpyAsync(small_of(p, ws), p->table_img.data(), p->table_img.size(), hipMemcpyHostToDevice, st));
+  if (!p->bt_img.empty())
+    QEW_HIP(hipMemcpyAsync(static_cast<char*>(ws) + p->lay.bt_s, p->bt_img.data(), p->bt_img.size() * 4,
+                           hipMemcpyHostToDevice, st));
   QEW_HIP(hipStreamSynchronize(st));
   return QEW_OK;
 }
@@ -380,9 +438,17 @@ hipError_t fused_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipSt
                            p->kind, p->tile, p->k, nsub, p->fused_grid, p->sparse != 0, st);
 }
 
-// The plan's stepping launch: fused (nsub steps) on the fused path, else one step.
+// Euler steps of a full launch of the plan's stepping kernel.
+int launch_steps(const qew_plan_t* p) { return fused(p) ? p->k : (p->bk ? p->bk : 1); }
+
+// The plan's stepping launch of nsub steps: the fused kernel on the fused
+// path, the blocked one for the FP64 state (a single step is cheaper on the
+// one-step kernel: 97 against 120 us at 2^22 x 4), else one step.
 hipError_t step_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipStream_t st) {
   if (fused(p)) return fused_launch(p, ws, from, nsub, st);
+  if (nsub > 1)
+    return launch_blocked_plain(tables_of(p, ws), plain_buf(p, ws, from), plain_buf(p, ws, from ^ 1), phys_of(p),
+                                p->kind, p->btile, p->bk, nsub, st);
   return onestep_launch(p, ws, from, nullptr, st);
 }
 
@@ -418,7 +484,7 @@ qew_status ensure_graph(qew_plan_t* p, void* ws) {
   QEW_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t le = hipSuccess;
   for (int i = 0; i < kGraphLaunches && le == hipSuccess; ++i)
-    le = step_launch(p, ws, i & 1, p->k, p->cap_stream);
+    le = step_launch(p, ws, i & 1, launch_steps(p), p->cap_stream);
   hipGraph_t graph = nullptr;
   const hipError_t ee = hipStreamEndCapture(p->cap_stream, &graph);
   if (le != hipSuccess || ee != hipSuccess) {
@@ -449,7 +515,7 @@ void count_launches(qew_plan_t* p, int64_t n, bool fused_kernel) {
 // Advance the state by n Euler steps with the plan's stepping kernel
 // (buffer parity tracked in the plan).
 qew_status advance(qew_plan_t* p, void* ws, int64_t n, hipStream_t st) {
-  const int kk = p->k;
+  const int kk = launch_steps(p);
   int64_t blocks = n / kk;
   const int rem = (int)(n % kk);
   const bool use_graph = !(p->flags & QEW_FLAG_NO_GRAPH) && !p->direct_only;
@@ -748,6 +814,7 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
   } else {
     p->k = 1;
     p->tile = 0;
+    build_blocked_tiles(p);
   }
   compute_layout(p);
   refresh_table_image(p);

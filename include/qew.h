@@ -182,7 +182,9 @@ qew_status qew_plan_info_get(const qew_plan_t *plan, qew_plan_info *info);
 
 /*
  * Choose k and the tile width of the fused path by timing short runs on the
- * workspace (its state is overwritten).  Called by qew_run by itself when the
+ * workspace (its state is overwritten).  Where the problem left both open and
+ * is small, narrow tiles (256 or 512 sites, up to 112 steps per launch) are
+ * taken by a rule on the number of tiles instead, unless a flag forces a variant.  Called by qew_run by itself when the
  * problem left k or tile at 0.  No-op for the one-step path.
  */
 qew_status qew_autotune(qew_plan_t *plan, void *d_ws, size_t ws_bytes, void *stream);

@@ -978,7 +978,8 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
 // pass of the generator.  The edges are published before that work, so the
 // barrier finds them written.  FP64, four chains of 1024 sites: 0.37 us per
 // step on 256-site tiles (the request path on them: 1.04, one step per launch:
-// 4.1), of which 0.2 us are the steps, the edges and the barrier.
+// 4.1), of which 0.2 us are the steps, the edges and the barrier.  Split state,
+// the same chains: 0.33 us against 0.92 of the 1024-site request tiles.
 // ---------------------------------------------------------------------------
 constexpr int kSpare = 4;
 
@@ -1567,6 +1568,13 @@ bool fused_fits(int tile) {
 template <int KIND, bool SPARSE>
 static void launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int tile,
                               int halo, int nsub, dim3 g, dim3 b, hipStream_t st) {
+  if constexpr (!SPARSE) {
+    if (tile == 256 || tile == 512) {  // one workgroup per tile
+      if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 1>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
+      else hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 2>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
+      return;
+    }
+  }
   if (tile == 1024) hipLaunchKernelGGL((k_step_fused<KIND, 4, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
   else if (tile == 1536) hipLaunchKernelGGL((k_step_fused<KIND, 6, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
   else if (tile == 2048) hipLaunchKernelGGL((k_step_fused<KIND, 8, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);

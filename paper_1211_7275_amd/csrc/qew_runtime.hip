@@ -146,6 +146,10 @@ namespace {
 
 bool fused(const qew_plan_t* p) { return p->path == QEW_FUSED; }
 
+// The fused path on the narrow tiles of k_lanes (small problems): no dense and
+// sparse variants there.
+bool lanes(const qew_plan_t* p) { return fused(p) && p->tile < 1024; }
+
 void refresh_table_image(qew_plan_t* p);
 int64_t fused_tile_count(const qew_plan_t* p, int tile, int k);
 
@@ -165,6 +169,27 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
   p->k = k;
   p->tile = tile;
   if (p->lay.total) refresh_table_image(p);
+}
+
+// Narrow-tile geometry of the fused path (k_lanes), for small problems where
+// the caller left k and the tile open and forced no variant.  The candidates are
+// tried in order, each taken if it needs at most `most` workgroups.  Measured,
+// us per step (RF, four chains of L; last column: the tuner's wide tiles):
+//                256/112  256/96  256/64  512/64   wide
+//   L = 2^10       0.33     0.34    0.38    0.57   0.92
+//   L = 2^14       0.68     0.46    0.40    0.59   0.83
+//   L = 2^16       2.1      1.2     0.75    0.70   0.88
+//   L = 2^17       4.1      2.1     1.23    1.02   0.97
+bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
+  if (!fused(p) || p->k_req || p->tile_req || (p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
+  struct { int tile, k; int64_t most; } const geometry[] = {{256, 112, 256}, {256, 96, 256}, {256, 64, 1024}, {512, 64, 1152}};
+  for (const auto& g : geometry) {
+    if (fused_tile_count(p, g.tile, g.k) > g.most) continue;
+    *tile = g.tile;
+    *k = g.k;
+    return true;
+  }
+  return false;
 }
 
 // Geometry of the blocked FP64 kernels (none without disorder: a pure stencil
@@ -454,6 +479,10 @@ hipError_t step_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipStr
 
 qew_status ensure_fused_grid(qew_plan_t* p) {
   if (!fused(p)) return QEW_OK;
+  if (lanes(p)) {  // one workgroup per tile
+    p->fused_grid = (int)p->ft_s.size();
+    return QEW_OK;
+  }
   if (!fused_fits(p->tile)) return fail(QEW_EUNSUPPORTED, "tile %d needs more LDS than this device allows", p->tile);
   const int maxg = fused_max_grid(p->tile);
   if (maxg <= 0) return fail(QEW_EDEVICE, "could not query occupancy of the fused kernel");
@@ -571,6 +600,7 @@ qew_status advance_onestep(qew_plan_t* p, void* ws, int64_t n, Partial* part, hi
 // stretch was still queued behind them, so the wait leaves no gap on the
 // device.  A flag can force either variant.
 qew_status choose_variant(qew_plan_t* p) {
+  if (lanes(p)) return QEW_OK;
   if (p->flags & QEW_FLAG_FUSED_DENSE) { p->sparse = 0; return QEW_OK; }
   if (p->flags & QEW_FLAG_FUSED_SPARSE) { p->sparse = 1; return QEW_OK; }
   const int slot = p->rb_next;
@@ -798,6 +828,8 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
       }
     }
     if (p->k_req && p->tile_req) cap = fused_tile_count(p, p->tile_req, p->k_req);
+    int ntile = 0, nk = 0;
+    if (narrow_geometry(p, &ntile, &nk)) cap = std::max(cap, fused_tile_count(p, ntile, nk));
     if (cap == 0) {
       delete p;
       return fail(QEW_EINVAL, "no fused geometry satisfies 4*k <= tile");
@@ -855,7 +887,10 @@ qew_status qew_autotune(qew_plan_t* p, void* ws, size_t bytes, void* stream) {
   QEW_HIP(hipEventCreate(&e1));
   double best = -1.0;
   int best_tile = p->tile, best_k = p->k;
+  const bool narrow = narrow_geometry(p, &best_tile, &best_k);  // by rule, nothing to time
+  if (narrow) best = 1.0;
   for (int tile : kTuneTiles) {
+    if (narrow) break;
     if (p->tile_req && tile != p->tile_req) continue;
     if (!fused_fits(tile)) continue;
     for (int kc : kTuneK) {
@@ -1021,7 +1056,7 @@ static qew_status run_impl(qew_plan_t* p, void* ws, size_t bytes, hipStream_t st
         if ((rc = measure(p, ws, mi, st)) != QEW_OK) break;
         if ((he = close_ev(meas_ev)) != hipSuccess) break;
       }
-      if (fused(p) && !noalloc && (rc = post_velocities(p, ws, mi, st)) != QEW_OK) break;
+      if (fused(p) && !lanes(p) && !noalloc && (rc = post_velocities(p, ws, mi, st)) != QEW_OK) break;
       ++mi;
     }
     if (n > 0 && onestep) {

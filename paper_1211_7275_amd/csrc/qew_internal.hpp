@@ -107,15 +107,15 @@ size_t critical_lds_bytes(int L);
 hipError_t launch_critical(int kind, const CritParams& q, int n_samples, const uint32_t* did, double* u_io,
                            double* f_out, int64_t* st_out, hipStream_t st);
 
-// Structure factor at one measurement: pack, FFT passes, per-mode |U_n/L|^2,
+// Structure factor at one measurement: FFT from the chain to per-mode |U_n/L|^2,
 // binned mean over samples into out[n_bins].  Every L_s equals L (power of
 // two, at least 8); u_plain != nullptr selects the FP64 state, else `split`.
 // The bins are cut into n_chunks chunks of modes [chunk_lo[c], chunk_lo[c+1])
 // (bin b owns chunks chunk_first[b] .. chunk_first[b+1]-1); `part` holds one
-// partial sum per chunk.
+// partial sum per chunk; no bin has more than `max_bin` modes.
 hipError_t launch_sq(const int64_t* off, int S, int64_t L, const double* u_plain, SplitBuf split,
                      double2* bufA, double2* bufB, const int32_t* chunk_lo, int n_chunks,
-                     const int32_t* chunk_first, int n_bins, double* part, double* out,
+                     const int32_t* chunk_first, int n_bins, int max_bin, double* part, double* out,
                      hipStream_t st);
 
 }  // namespace qew

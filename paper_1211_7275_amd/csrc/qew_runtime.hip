@@ -101,7 +101,7 @@ struct GraphCache {
 struct qew_plan_s {
   // problem
   int32_t S = 0, kind = 0, precision = 0, path = 0, k_req = 0, tile_req = 0, flags = 0, period = 0;
-  int32_t sq_bins = 0;
+  int32_t sq_bins = 0, sq_max_bin = 0;  // bins and the widest one's modes
   std::vector<int64_t> sq_edges;
   std::vector<int32_t> sq_chunk_lo;     // [n_chunks + 1] mode ranges of the binning chunks
   std::vector<int32_t> sq_chunk_first;  // [sq_bins + 1] first chunk of each bin
@@ -645,7 +645,7 @@ qew_status measure_finish(qew_plan_t* p, void* ws, int mi, int buf, hipStream_t 
                       reinterpret_cast<double2*>(b + p->lay.fftA), reinterpret_cast<double2*>(b + p->lay.fftB),
                       reinterpret_cast<const int32_t*>(b + p->lay.sq_chunk_lo),
                       (int)p->sq_chunk_lo.size() - 1, reinterpret_cast<const int32_t*>(b + p->lay.sq_chunk_first),
-                      p->sq_bins, reinterpret_cast<double*>(b + p->lay.sq_part),
+                      p->sq_bins, p->sq_max_bin, reinterpret_cast<double*>(b + p->lay.sq_part),
                       reinterpret_cast<double*>(b + p->lay.sq_series) + (size_t)mi * p->sq_bins, st));
   }
   p->stats.meas_launches++;
@@ -780,6 +780,7 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
     // Each bin is cut into chunks of at most kSqChunk modes, summed by one
     // workgroup each; a bin then adds its chunks' sums in order.
     for (int32_t b = 0; b < p->sq_bins; ++b) {
+      p->sq_max_bin = std::max(p->sq_max_bin, (int32_t)(p->sq_edges[b + 1] - p->sq_edges[b]));
       p->sq_chunk_first.push_back((int32_t)p->sq_chunk_lo.size());
       for (int64_t lo = p->sq_edges[b]; lo < p->sq_edges[b + 1]; lo += kSqChunk)
         p->sq_chunk_lo.push_back((int32_t)lo);

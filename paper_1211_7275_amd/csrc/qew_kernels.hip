@@ -272,9 +272,9 @@ __global__ void __launch_bounds__(kBlock)
 //      windows and replies belong to one wave and a wave's LDS operations
 //      complete in order, so this needs no workgroup barrier;
 //   4. the wave publishes its end sites; one workgroup barrier.
-// A wave posts at most kReqPerWave requests per sub-step; the lanes of further
-// requests (a burst of simultaneous cell changes) regenerate their windows
-// themselves.  After nsub <= halo sub-steps the sites within `halo` of either
+// A wave serves kReqPerWave requests at a time; further ones (a burst of
+// simultaneous cell changes) take further rounds, or on wide tiles their lanes
+// regenerate the windows themselves.  After nsub <= halo sub-steps the sites within `halo` of either
 // tile end hold garbage (the tile ends reflect), and the valid part
 // [halo, halo + len) is written back with its nodes.  Every value equals what
 // the one-step kernel computes: the float cell differences are exact integers
@@ -495,8 +495,7 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
       // wave only, and a wave's LDS operations complete in program order, so
       // no workgroup barrier is needed between posting, serving and reading.
       __builtin_amdgcn_s_setprio(0);
-      const uint32_t nserve = nreq < (uint32_t)RQ ? nreq : (uint32_t)RQ;
-      if (nserve > 0u) {
+      auto serve = [&](uint32_t nserve) __attribute__((always_inline)) {
         __builtin_amdgcn_wave_barrier();
         if ((uint32_t)lane < nserve) {
           const int slot = rbase + lane;
@@ -517,10 +516,9 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
           } else if (move == -1.0f) {
             w4 = make_float4(node_f32<KIND>((uint32_t)j, cell - 1, id, ph.k0, ph.k1, ph.period), w4.x, w4.y, w4.z);
           } else {
-            w4 = make_float4(node_f32<KIND>((uint32_t)j, cell - 1, id, ph.k0, ph.k1, ph.period),
-                             node_f32<KIND>((uint32_t)j, cell, id, ph.k0, ph.k1, ph.period),
-                             node_f32<KIND>((uint32_t)j, cell + 1, id, ph.k0, ph.k1, ph.period),
-                             node_f32<KIND>((uint32_t)j, cell + 2, id, ph.k0, ph.k1, ph.period));
+#pragma unroll 1
+            for (int m = cell - 1; m <= cell + 2; ++m)
+              w4 = make_float4(w4.y, w4.z, w4.w, node_f32<KIND>((uint32_t)j, m, id, ph.k0, ph.k1, ph.period));
           }
           s_nodes[ni] = w4;
           float4 co;
@@ -531,24 +529,51 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-      }
-      // Requesters read their new coefficients (a request past the region
-      // reads its sink slot and is redone below); a wave without requests
-      // skips the slot checks.
-      if (nreq > 0u) {
+      };
+      auto read_back = [&](int i, uint32_t at) __attribute__((always_inline)) {
+        const int4 v = *reinterpret_cast<const int4*>(reinterpret_cast<const char*>(s_req) + at);
+        a[i] = make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z), __int_as_float(v.w));
+      };
+      const uint32_t nserve = nreq < (uint32_t)RQ ? nreq : (uint32_t)RQ;
+      if (nserve > 0u) {
+        serve(nserve);
+        // Requesters read their new coefficients (a request past the region
+        // reads its sink slot and is served below).
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-          if (c[i] != oc[i]) {
-            const int4 v = *reinterpret_cast<const int4*>(reinterpret_cast<const char*>(s_req) + kb[i]);
-            a[i] = make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z),
-                               __int_as_float(v.w));
-          }
-        }
+        for (int i = 0; i < P; ++i)
+          if (c[i] != oc[i]) read_back(i, kb[i]);
         __builtin_amdgcn_wave_barrier();
       }
       // Rare: more requests than the region holds (a burst of cell changes).
-      // Those past it regenerate their window on their own lane.
-      if (nreq > (uint32_t)RQ) {
+      // Those past it are posted and served in further rounds; on tiles of 12
+      // or more sites per thread, where the rounds' code costs the common path
+      // 3 % (measured), their lanes make their windows themselves.  At
+      // 2^22 x 4 on 2048-site tiles, k = 56, ms per launch, that and the rounds:
+      // f = 1.0 0.692, 0.678; f = 2.5 1.165, 1.042; random bond f = 4 2.563, 1.392.
+      if constexpr (P <= 8) {
+#pragma unroll 1
+        for (uint32_t done = RQ; done < nreq; done += RQ) {
+          uint32_t first = 0u;
+          bool mine[P];
+#pragma unroll
+          for (int i = 0; i < P; ++i) {
+            const bool mv = c[i] != oc[i];
+            const uint64_t moved = __ballot(mv);
+            const uint32_t r = first + mbcnt64(moved) - done;
+            mine[i] = mv && r < (uint32_t)RQ;
+            kb[i] = rbase_b + r * (uint32_t)sizeof(int4);
+            if (mine[i])
+              *reinterpret_cast<int3*>(reinterpret_cast<char*>(s_req) + kb[i]) = make_int3(
+                  i * kBlock + tid, __float_as_int(par ? oc[i] : c[i]), __float_as_int(par ? c[i] : oc[i]));
+            first += (uint32_t)__popcll(moved);
+          }
+          serve(nreq - done < (uint32_t)RQ ? nreq - done : (uint32_t)RQ);
+#pragma unroll
+          for (int i = 0; i < P; ++i)
+            if (mine[i]) read_back(i, kb[i]);
+          __builtin_amdgcn_wave_barrier();
+        }
+      } else if (nreq > (uint32_t)RQ) {
 #pragma unroll
         for (int i = 0; i < P; ++i) {
           if (c[i] != oc[i] && kb[i] == sink_b) {

@@ -78,8 +78,9 @@ hipError_t launch_meas_plain(const Tables& t, const double* u, const Phys& ph, i
 // of regenerated.
 hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int kind, Partial* part,
                              hipStream_t st);
+// v_host: null, or host memory the kernel also writes every sample's velocity to.
 hipError_t launch_meas_final(const Tables& t, int n_samples, const Partial* part, int meas_index,
-                             int n_meas, double* series, hipStream_t st);
+                             int n_meas, double* series, double* v_host, hipStream_t st);
 hipError_t launch_ensemble(int n_samples, int n_meas, const double* series, double* out,
                            hipStream_t st);
 hipError_t launch_fill_f64(double* p, int64_t n, double value, hipStream_t st);

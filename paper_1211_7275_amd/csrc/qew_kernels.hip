@@ -1343,7 +1343,7 @@ __device__ __forceinline__ Moments combine(const Moments& a, const Moments& b) {
 }
 
 __global__ void __launch_bounds__(kBlock)
-    k_meas_final(Tables t, const Partial* part, int meas_index, int n_meas, double* series) {
+    k_meas_final(Tables t, const Partial* part, int meas_index, int n_meas, double* series, double* v_host) {
   __shared__ Moments lds[kBlock];
   const int s = blockIdx.x;
   const int t0 = t.mt_first[s], t1 = t.mt_first[s + 1];
@@ -1368,7 +1368,9 @@ __global__ void __launch_bounds__(kBlock)
     const Moments m = lds[0];
     const double L = (double)t.L[s];
     double* out = series + ((int64_t)s * n_meas + meas_index) * 3;
-    out[0] = m.sf / L;
+    const double v = m.sf / L;
+    out[0] = v;
+    if (v_host) v_host[s] = v;  // pinned host memory
     out[1] = m.mean;
     out[2] = (m.m2 > 0.0 ? m.m2 : 0.0) / L;
   }
@@ -1639,9 +1641,9 @@ hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int ki
 }
 
 hipError_t launch_meas_final(const Tables& t, int n_samples, const Partial* part, int meas_index,
-                             int n_meas, double* series, hipStream_t st) {
+                             int n_meas, double* series, double* v_host, hipStream_t st) {
   hipLaunchKernelGGL(k_meas_final, dim3(n_samples), dim3(kBlock), 0, st, t, part, meas_index, n_meas,
-                     series);
+                     series, v_host);
   return hipGetLastError();
 }
 

@@ -615,14 +615,17 @@ qew_status choose_variant(qew_plan_t* p) {
   return QEW_OK;
 }
 
-// After measurement mi: send the velocities of every sample to the host
-// (next slot).
-qew_status post_velocities(qew_plan_t* p, void* ws, int mi, hipStream_t st) {
+// Whether the run follows the line's velocity (choose_variant).
+bool follows_velocity(const qew_plan_t* p) {
+  return fused(p) && !lanes(p) && !p->direct_only && !(p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE));
+}
+
+// After a measurement whose last kernel wrote the velocities of every sample
+// into the next slot of rb_host: mark when they are there.  (A copy of them
+// from the device series, 8 bytes per sample at a stride, held the stream for
+// 20 us at every measurement.)
+qew_status post_velocities(qew_plan_t* p, hipStream_t st) {
   const int slot = p->rb_next;
-  const size_t n_meas = p->meas.size();
-  const double* v = series_of(p, ws) + (size_t)mi * 3;
-  QEW_HIP(hipMemcpy2DAsync(p->rb_host + (size_t)slot * p->S, sizeof(double), v, n_meas * 3 * sizeof(double),
-                           sizeof(double), (size_t)p->S, hipMemcpyDeviceToHost, st));
   QEW_HIP(hipEventRecord(p->rb_event[slot], st));
   p->rb_valid[slot] = true;
   p->rb_next ^= 1;
@@ -636,7 +639,8 @@ qew_status post_velocities(qew_plan_t* p, void* ws, int mi, hipStream_t st) {
 qew_status measure_finish(qew_plan_t* p, void* ws, int mi, int buf, hipStream_t st) {
   const Tables t = tables_of(p, ws);
   double* series = series_of(p, ws);
-  QEW_HIP(launch_meas_final(t, p->S, partials_of(p, ws), mi, (int)p->meas.size(), series, st));
+  QEW_HIP(launch_meas_final(t, p->S, partials_of(p, ws), mi, (int)p->meas.size(), series,
+                            follows_velocity(p) ? p->rb_host + (size_t)p->rb_next * p->S : nullptr, st));
   if (p->sq_bins > 0) {
     char* b = static_cast<char*>(ws);
     const bool plain = p->precision == QEW_FP64_PLAIN;
@@ -970,9 +974,10 @@ static qew_status run_impl(qew_plan_t* p, void* ws, size_t bytes, hipStream_t st
   if (noalloc && resume)  // this plan's series so far, from the workspace
     QEW_HIP(hipMemcpyAsync(series_of(p, ws), static_cast<char*>(ws) + p->lay.series,
                            (size_t)p->S * p->meas.size() * 3 * sizeof(double), hipMemcpyDeviceToDevice, st));
-  if (fused(p) && !noalloc) {
-    if (!p->rb_host)
-      QEW_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->rb_host), 2 * (size_t)p->S * sizeof(double)));
+  if (follows_velocity(p)) {
+    if (!p->rb_host)  // coherent: the kernel's stores are in host memory when it has ended
+      QEW_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->rb_host), 2 * (size_t)p->S * sizeof(double),
+                            hipHostMallocMapped | hipHostMallocCoherent));
     for (int i = 0; i < 2; ++i) {
       if (!p->rb_event[i]) QEW_HIP(hipEventCreateWithFlags(&p->rb_event[i], hipEventDisableTiming));
       p->rb_valid[i] = false;
@@ -1057,7 +1062,7 @@ static qew_status run_impl(qew_plan_t* p, void* ws, size_t bytes, hipStream_t st
         if ((rc = measure(p, ws, mi, st)) != QEW_OK) break;
         if ((he = close_ev(meas_ev)) != hipSuccess) break;
       }
-      if (fused(p) && !lanes(p) && !noalloc && (rc = post_velocities(p, ws, mi, st)) != QEW_OK) break;
+      if (follows_velocity(p) && (rc = post_velocities(p, st)) != QEW_OK) break;
       ++mi;
     }
     if (n > 0 && onestep) {

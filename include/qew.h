@@ -260,7 +260,8 @@ qew_status qew_run_stats_get(const qew_plan_t *plan, qew_run_stats *stats);
 
 /*
  * Copy sample s's state (step index `*h_step`) to h_u [L_s] as FP64
- * (cell + offset for the split precision).  Synchronous.
+ * (cell + offset for the split precision, joined on the device in the
+ * workspace's other state buffer).  Synchronous.
  */
 qew_status qew_read_state(const qew_plan_t *plan, const void *d_ws, void *stream, int32_t s,
                           double *h_u, int64_t *h_step);

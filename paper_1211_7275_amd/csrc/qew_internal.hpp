@@ -83,6 +83,7 @@ hipError_t launch_meas_final(const Tables& t, int n_samples, const Partial* part
                              int n_meas, double* series, double* v_host, hipStream_t st);
 hipError_t launch_ensemble(int n_samples, int n_meas, const double* series, double* out,
                            hipStream_t st);
+hipError_t launch_join_split(const int32_t* cell, const float* frac, double* u, int64_t n, hipStream_t st);
 hipError_t launch_fill_f64(double* p, int64_t n, double value, hipStream_t st);
 hipError_t launch_fill_i32(int* p, int64_t n, int value, hipStream_t st);
 hipError_t launch_philox_fill(const uint32_t* ctr, uint32_t k0, uint32_t k1, uint32_t* out,

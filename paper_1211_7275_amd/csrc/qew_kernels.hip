@@ -1416,6 +1416,13 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
+// u = cell + offset of a chain in the split state.
+__global__ void __launch_bounds__(kBlock)
+    k_join_split(const int32_t* __restrict__ cell, const float* __restrict__ frac, double* __restrict__ u, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) u[i] = (double)cell[i] + (double)frac[i];
+}
+
 __global__ void k_fill_i32(int* p, int64_t n, int value) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) p[i] = value;
@@ -1651,6 +1658,12 @@ hipError_t launch_ensemble(int n_samples, int n_meas, const double* series, doub
                            hipStream_t st) {
   if (n_meas <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_ensemble, dim3(n_meas), dim3(kBlock), 0, st, n_samples, n_meas, series, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_join_split(const int32_t* cell, const float* frac, double* u, int64_t n, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_join_split, dim3((uint32_t)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, cell, frac, u, n);
   return hipGetLastError();
 }
 

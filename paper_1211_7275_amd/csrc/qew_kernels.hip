@@ -1001,10 +1001,13 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
 // enters the next cell only forms its coefficients.  When a lane has no node
 // left, the whole wave makes one node ahead for every lane with room, in one
 // pass of the generator.  The edges are published before that work, so the
-// barrier finds them written.  FP64, four chains of 1024 sites: 0.37 us per
-// step on 256-site tiles (the request path on them: 1.04, one step per launch:
-// 4.1), of which 0.2 us are the steps, the edges and the barrier.  Split state,
-// the same chains: 0.33 us against 0.92 of the 1024-site request tiles.
+// barrier finds them written, by every lane (a taken branch costs some 40
+// cycles here, as much as ten operations).  FP64, four chains of 1024 sites: 0.35
+// us per step on 256-site tiles (the request path on them: 1.04, one step per
+// launch: 4.1), of which 0.2 us are the steps, the edges and the barrier.  Split
+// state, the same chains: 0.32 us against 0.92 of the 1024-site request tiles.
+// Measured and dropped: the nodes ahead in registers (0.34), coefficients of
+// unit strength in a branch of their own (0.37).
 // ---------------------------------------------------------------------------
 constexpr int kSpare = 4;
 
@@ -1132,7 +1135,10 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
   using node_t = typename A::node_t;
   using edge_t = typename A::edge_t;
   __shared__ node_t s_ahead[kSpare][T];    // node m of a site in row m mod kSpare
-  __shared__ edge_t s_edge[2][NW + 2][2];  // end sites of each wave, double-buffered
+  // End sites of each wave, double-buffered, and behind them a place for every
+  // other lane to write to, so that the publishing needs no branch.
+  constexpr int kOther = (NW + 2) * 2;  // from one buffer to the other
+  __shared__ edge_t s_edge[2 * kOther + kBlock + kOther];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1177,13 +1183,13 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
   // Lanes 0 and 63 publish their wave's ends and read its neighbours' ends, one
   // LDS access each.  Beyond the tile's ends stand their first values: what
   // that spoils stays within nsub sites of the end.
-  const bool end_lane = lane == 0 || lane == 63;
-  edge_t* const mine = &s_edge[0][wv + 1][lane == 63 ? 1 : 0];
-  const edge_t* const theirs = lane == 63 ? &s_edge[0][wv + 2][0] : &s_edge[0][wv][1];
-  constexpr int kOther = (NW + 2) * 2;  // from one buffer of s_edge to the other
-  if (end_lane) *mine = A::edge(lane == 63 ? x[P - 1] : x[0]);
-  if (tid == 0) s_edge[0][0][1] = s_edge[1][0][1] = A::edge(x[0]);
-  if (tid == kBlock - 1) s_edge[0][NW + 1][0] = s_edge[1][NW + 1][0] = A::edge(x[P - 1]);
+  // Entry (w, e): end e of wave w - 1.
+  const int own = 2 * (wv + 1) + (lane == 63 ? 1 : 0);
+  edge_t* const mine = &s_edge[lane == 0 || lane == 63 ? own : 2 * kOther + tid];
+  const edge_t* const theirs = &s_edge[lane == 63 ? 2 * (wv + 2) : 2 * wv + 1];
+  *mine = A::edge(lane == 63 ? x[P - 1] : x[0]);
+  if (tid == 0) s_edge[1] = s_edge[kOther + 1] = A::edge(x[0]);
+  if (tid == kBlock - 1) s_edge[2 * (NW + 1)] = s_edge[kOther + 2 * (NW + 1)] = A::edge(x[P - 1]);
   __syncthreads();
 
   auto substep = [&](const int par) __attribute__((always_inline)) {
@@ -1201,12 +1207,12 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
       d[i] = A::step(x[i], prev, nb, k);
       prev = old;
     }
-    if (end_lane) mine[(par ^ 1) * kOther] = A::edge(lane == 63 ? x[P - 1] : x[0]);
+    mine[(par ^ 1) * kOther] = A::edge(lane == 63 ? x[P - 1] : x[0]);
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-      if (!__any(d[i] != 0)) continue;
+      if (__ballot(d[i] != 0) == 0u) continue;
       const bool up = d[i] == 1;
-      if (__any(up && ahead[i] == 0)) {
+      if (__ballot(up && ahead[i] == 0) != 0u) {
         if (ahead[i] < kSpare) {
           const int32_t m = A::cell(x[i], cbase) - (up ? 1 : 0) + A::kHigh + 1 + ahead[i];
           const node_t nd = A::node((uint32_t)col[i], m, id, ph);
@@ -1222,7 +1228,7 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
         next[i] = s_ahead[(A::cell(x[i], cbase) + A::kHigh + 1) & (kSpare - 1)][i * kBlock + tid];
       }
       const bool other = d[i] != 0 && !up;
-      if (__any(other)) {  // rare: backwards, or more than one cell
+      if (__ballot(other) != 0u) {  // rare: backwards, or more than one cell
         if (other) {
           fresh(x[i], col[i]);
           A::coef(x[i], k);

@@ -83,7 +83,7 @@ def _elf_sections(data):
 # every dense fused instantiation, and the FP64 one-step kernel of the
 # benchmark's disorder (random field) without measurement.
 FUSED_SYMBOLS = rb"k_step_fusedILi\d+ELi\d+ELb0E"
-PLAIN_SYMBOLS = rb"k_step_plainILi0ELb0E"
+PLAIN_SYMBOLS = rb"k_step_plainILi0ELi0E"
 
 
 def kernel_source_hash(pattern=FUSED_SYMBOLS):

@@ -43,6 +43,17 @@ struct Partial {
   double sum_f, s1, s2, shift;
 };
 
+// Where a measuring launch puts its sums: the tile partials (launch_meas_final
+// then combines them), or, with groups > 0, straight into the series (every
+// sample has at most `groups` measurement tiles, 1 or 2).
+struct MeasOut {
+  Partial* part;     // null: no measurement
+  double* series;    // [S][n_meas][3]
+  double* v_host;    // null, or host memory that also receives every sample's velocity
+  int32_t mi, n_meas, n_samples, groups;
+};
+
+constexpr int kFinalTiles = 2;    // most tiles of a sample that one workgroup measures
 constexpr int kMeasTile = 4096;   // sites per measurement / one-step tile
 constexpr int kBlock = 256;       // threads per workgroup of every kernel
 constexpr int kMaxHalo = 128;
@@ -53,18 +64,17 @@ hipError_t launch_init_split(const Tables& t, SplitBuf b, const Phys& ph, int ki
                              hipStream_t st);
 hipError_t launch_refresh_nodes(const Tables& t, SplitBuf b, const Phys& ph, int kind,
                                 hipStream_t st);
-// One Euler step of every site; with `part` non-null the same launch also
-// writes the measurement partials of the input state (the partials
-// launch_meas_* would write, bit for bit).
+// One Euler step of every site; with o.part non-null the same launch also
+// measures the input state (what launch_meas_* would write, bit for bit).
 hipError_t launch_step_plain(const Tables& t, const double* uin, double* uout, const Phys& ph,
-                             int kind, Partial* part, hipStream_t st);
+                             int kind, const MeasOut& o, hipStream_t st);
 // nsub <= halo Euler steps of the FP64 state on the tiles of the list ft_* (T = `tile`
 // sites per workgroup: 512 or 256 for small problems, else blocked_wide_tile(kind)).
 constexpr int blocked_wide_tile(int kind) { return kind == 1 ? 1024 : 2048; }
 hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout, const Phys& ph, int kind,
                                 int tile, int halo, int nsub, hipStream_t st);
 hipError_t launch_step_split1(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
-                              Partial* part, hipStream_t st);
+                              const MeasOut& o, hipStream_t st);
 // `sparse`: the variant that skips the request bookkeeping of a wave whose
 // sites did not change cell (for pinned or slow lines).
 hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
@@ -72,15 +82,13 @@ hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const P
 int fused_max_grid(int tile);
 bool fused_fits(int tile);  // static LDS of the tile's kernel within the device limit
 hipError_t launch_meas_plain(const Tables& t, const double* u, const Phys& ph, int kind,
-                             Partial* part, hipStream_t st);
+                             const MeasOut& o, hipStream_t st);
 // Split state: b.nodes non-null means it holds the four nodes of every
 // site's current cell (the fused path's cache), which are then read instead
 // of regenerated.
-hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int kind, Partial* part,
+hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int kind, const MeasOut& o,
                              hipStream_t st);
-// v_host: null, or host memory the kernel also writes every sample's velocity to.
-hipError_t launch_meas_final(const Tables& t, int n_samples, const Partial* part, int meas_index,
-                             int n_meas, double* series, double* v_host, hipStream_t st);
+hipError_t launch_meas_final(const Tables& t, const MeasOut& o, hipStream_t st);
 hipError_t launch_ensemble(int n_samples, int n_meas, const double* series, double* out,
                            hipStream_t st);
 hipError_t launch_join_split(const int32_t* cell, const float* frac, double* u, int64_t n, hipStream_t st);

@@ -61,19 +61,20 @@ __device__ __forceinline__ uint32_t mbcnt64(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Block-wide deterministic FP64 sum of three values (fixed reduction order).
-__device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double* lds /*[3*4]*/) {
+// Deterministic FP64 sum of three values over a group of kBlock threads (thread
+// `tid` of it; fixed reduction order; the whole workgroup takes part).
+__device__ __forceinline__ void group_sum3(double& a, double& b, double& c, int tid, double* lds /*[3*4]*/) {
   a = wave_sum_f64(a);
   b = wave_sum_f64(b);
   c = wave_sum_f64(c);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
+  const int w = tid >> 6;
+  if ((tid & 63) == 0) {
     lds[w * 3 + 0] = a;
     lds[w * 3 + 1] = b;
     lds[w * 3 + 2] = c;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     double x = 0.0, y = 0.0, z = 0.0;
     for (int i = 0; i < kBlock / 64; ++i) {
       x += lds[i * 3 + 0];
@@ -85,8 +86,95 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
     c = z;
   }
 }
+__device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double* lds) {
+  group_sum3(a, b, c, (int)threadIdx.x, lds);
+}
 
 }  // namespace
+
+// Per-sample combine of tile partials: mean and sum of squared deviations by
+// the pairwise update of Chan, Golub and LeVeque, in a fixed order.
+struct Moments {
+  double n, mean, m2, sf;
+};
+
+__device__ __forceinline__ Moments combine(const Moments& a, const Moments& b) {
+  if (a.n == 0.0) return b;
+  if (b.n == 0.0) return a;
+  const double n = a.n + b.n;
+  const double d = b.mean - a.mean;
+  Moments r;
+  r.n = n;
+  r.mean = a.mean + d * (b.n / n);
+  r.m2 = (a.m2 + b.m2) + d * d * (a.n * b.n / n);
+  r.sf = a.sf + b.sf;
+  return r;
+}
+
+__device__ __forceinline__ Moments moments_of(const Partial& p, int len) {
+  const double n = (double)len;
+  return Moments{n, p.shift + p.s1 / n, p.s2 - p.s1 * (p.s1 / n), p.sum_f};
+}
+
+// Sample s's v, ubar, w2 at measurement o.mi.
+__device__ __forceinline__ void write_series(const Tables& t, const MeasOut& o, int s, const Moments& m) {
+  const double L = (double)t.L[s];
+  double* out = o.series + ((int64_t)s * o.n_meas + o.mi) * 3;
+  const double v = m.sf / L;
+  out[0] = v;
+  out[1] = m.mean;
+  out[2] = (m.m2 > 0.0 ? m.m2 : 0.0) / L;
+  if (o.v_host) o.v_host[s] = v;  // pinned host memory
+}
+
+// What a measuring launch does with its sums.  kFinal (every sample has at
+// most kFinalTiles tiles): a workgroup takes a whole sample, kBlock threads per
+// tile, combines its tiles in k_meas_final's order and writes the series: a
+// measurement is one launch less (L = 1024 x 4 over 10^4 steps with 50: 3.98 ->
+// 3.82 ms).  Four tiles of a sample on one CU cost more than that launch (24
+// lines of 2^14 sites with 60 measurements: 4.67 -> 4.85 ms).
+enum { kNoMeas = 0, kPartials = 1, kFinal = 2 };
+constexpr int meas_block(int mode) { return mode == kFinal ? kBlock * kFinalTiles : kBlock; }
+
+// The measurement tile of this thread's group, and the thread within it.
+struct TileOf {
+  int tile, s, tid;
+  bool valid;
+};
+template <int MODE>
+__device__ __forceinline__ TileOf tile_of(const Tables& t) {
+  if constexpr (MODE == kFinal) {
+    const int s = blockIdx.x;
+    const int tile = t.mt_first[s] + uniform_i32((int)(threadIdx.x / kBlock));
+    return TileOf{tile, s, (int)(threadIdx.x % kBlock), tile < t.mt_first[s + 1]};
+  } else {
+    return TileOf{(int)blockIdx.x, t.mt_s[blockIdx.x], (int)threadIdx.x, true};
+  }
+}
+
+struct MeasLds {
+  double sum[3 * (kBlock / 64) * kFinalTiles];
+  Moments m[kFinalTiles];
+};
+
+template <int MODE>
+__device__ __forceinline__ void emit(const Tables& t, const MeasOut& o, const TileOf& w, int len, double sf, double s1,
+                                     double s2, double shift, MeasLds& lds) {
+  if constexpr (MODE == kPartials) {
+    block_sum3(sf, s1, s2, lds.sum);
+    if (threadIdx.x == 0) o.part[w.tile] = Partial{sf, s1, s2, shift};
+  } else {
+    const int g = threadIdx.x / kBlock;
+    group_sum3(sf, s1, s2, w.tid, lds.sum + g * 3 * (kBlock / 64));
+    if (w.tid == 0) lds.m[g] = w.valid ? moments_of(Partial{sf, s1, s2, shift}, len) : Moments{0.0, 0.0, 0.0, 0.0};
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      Moments m = lds.m[0];
+      if (blockDim.x > kBlock) m = combine(m, lds.m[1]);
+      write_series(t, o, w.s, m);
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Initialisation: flat start u = 0 (Sec. II).
@@ -149,17 +237,17 @@ __global__ void __launch_bounds__(kBlock) k_refresh_nodes(Tables t, SplitBuf b, 
 // ---------------------------------------------------------------------------
 // One-step kernels (one Euler step per launch).
 // ---------------------------------------------------------------------------
-// MEAS: also write the measurement partial of the input state (the same
-// loop, forces and reduction order as k_meas_plain, so the partials are the
-// same bits), so a measured step reads the state once.
-template <int KIND, bool MEAS>
-__global__ void __launch_bounds__(kBlock)
+// MODE != kNoMeas: also measure the input state (the same loop, forces and
+// reduction order as k_meas_plain, so the sums are the same bits), so a
+// measured step reads the state once.
+template <int KIND, int MODE>
+__global__ void __launch_bounds__(meas_block(MODE))
     k_step_plain(Tables t, const double* __restrict__ uin, double* __restrict__ uout, Phys ph,
-                 Partial* part) {
-  __shared__ double lds[MEAS ? 3 * (kBlock / 64) : 1];
-  const int tile = blockIdx.x;
-  const int s = t.mt_s[tile];
-  const int p0 = t.mt_p0[tile], len = t.mt_len[tile];
+                 MeasOut o) {
+  constexpr bool MEAS = MODE != kNoMeas;
+  const TileOf w = tile_of<MODE>(t);
+  const int s = w.s;
+  const int p0 = w.valid ? t.mt_p0[w.tile] : 0, len = w.valid ? t.mt_len[w.tile] : 0;
   const int L = t.L[s];
   const int64_t base = t.off[s];
   const uint32_t id = t.did[s];
@@ -168,7 +256,7 @@ __global__ void __launch_bounds__(kBlock)
   const VectorKeys keys = vector_keys(ph.k0, ph.k1);
   const double K = MEAS ? uin[base + p0] : 0.0;
   double sf = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int q = threadIdx.x; q < len; q += kBlock) {
+  for (int q = w.tid; q < len; q += kBlock) {
     const int j = p0 + q;
     const int jm = (j == 0) ? L - 1 : j - 1;
     const int jp = (j == L - 1) ? 0 : j + 1;
@@ -184,8 +272,8 @@ __global__ void __launch_bounds__(kBlock)
     }
   }
   if constexpr (MEAS) {
-    block_sum3(sf, s1, s2, lds);
-    if (threadIdx.x == 0) part[tile] = Partial{sf, s1, s2, K};
+    __shared__ MeasLds lds;
+    emit<MODE>(t, o, w, len, sf, s1, s2, K, lds);
   }
 }
 
@@ -205,15 +293,15 @@ __device__ __forceinline__ void nodes_of(uint32_t j, int32_t c, uint32_t id, con
   p3 = cubic ? node_f32<KIND>(j, c + 2, id, keys, ph.period) : 0.0f;
 }
 
-// MEAS: also write the measurement partial of the input state, as
-// k_meas_split computes it (same loop, forces and reduction order).
-template <int KIND, bool MEAS>
-__global__ void __launch_bounds__(kBlock)
-    k_step_split1(Tables t, SplitBuf in, SplitBuf out, Phys ph, Partial* part) {
-  __shared__ double lds[MEAS ? 3 * (kBlock / 64) : 1];
-  const int tile = blockIdx.x;
-  const int s = t.mt_s[tile];
-  const int p0 = t.mt_p0[tile], len = t.mt_len[tile];
+// MODE != kNoMeas: also measure the input state, as k_meas_split does (same
+// loop, forces and reduction order).
+template <int KIND, int MODE>
+__global__ void __launch_bounds__(meas_block(MODE))
+    k_step_split1(Tables t, SplitBuf in, SplitBuf out, Phys ph, MeasOut o) {
+  constexpr bool MEAS = MODE != kNoMeas;
+  const TileOf w = tile_of<MODE>(t);
+  const int s = w.s;
+  const int p0 = w.valid ? t.mt_p0[w.tile] : 0, len = w.valid ? t.mt_len[w.tile] : 0;
   const int L = t.L[s];
   const int64_t base = t.off[s];
   const uint32_t id = t.did[s];
@@ -223,7 +311,7 @@ __global__ void __launch_bounds__(kBlock)
   const double Kr = MEAS ? (double)in.frac[base + p0] : 0.0;
   const VectorKeys keys = vector_keys(ph.k0, ph.k1);
   double sf = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int q = threadIdx.x; q < len; q += kBlock) {
+  for (int q = w.tid; q < len; q += kBlock) {
     const int j = p0 + q;
     const int jm = (j == 0) ? L - 1 : j - 1;
     const int jp = (j == L - 1) ? 0 : j + 1;
@@ -245,8 +333,8 @@ __global__ void __launch_bounds__(kBlock)
     out.frac[base + j] = r;
   }
   if constexpr (MEAS) {
-    block_sum3(sf, s1, s2, lds);
-    if (threadIdx.x == 0) part[tile] = Partial{sf, s1, s2, (double)Kc + Kr};
+    __shared__ MeasLds lds;
+    emit<MODE>(t, o, w, len, sf, s1, s2, (double)Kc + Kr, lds);
   }
 }
 
@@ -1256,13 +1344,13 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
 // ---------------------------------------------------------------------------
 // Measurement partials (Eqs. (3)-(5)) of the state at one step.
 // ---------------------------------------------------------------------------
-template <int KIND>
-__global__ void __launch_bounds__(kBlock)
-    k_meas_plain(Tables t, const double* __restrict__ u, Phys ph, Partial* part) {
-  __shared__ double lds[3 * (kBlock / 64)];
-  const int tile = blockIdx.x;
-  const int s = t.mt_s[tile];
-  const int p0 = t.mt_p0[tile], len = t.mt_len[tile];
+template <int KIND, int MODE>
+__global__ void __launch_bounds__(meas_block(MODE))
+    k_meas_plain(Tables t, const double* __restrict__ u, Phys ph, MeasOut o) {
+  __shared__ MeasLds lds;
+  const TileOf w = tile_of<MODE>(t);
+  const int s = w.s;
+  const int p0 = w.valid ? t.mt_p0[w.tile] : 0, len = w.valid ? t.mt_len[w.tile] : 0;
   const int L = t.L[s];
   const int64_t base = t.off[s];
   const uint32_t id = t.did[s];
@@ -1271,7 +1359,7 @@ __global__ void __launch_bounds__(kBlock)
   const VectorKeys keys = vector_keys(ph.k0, ph.k1);
   const double K = u[base + p0];  // shift: the tile's first site (exactly 0 for a flat tile)
   double sf = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int q = threadIdx.x; q < len; q += kBlock) {
+  for (int q = w.tid; q < len; q += kBlock) {
     const int j = p0 + q;
     const int jm = (j == 0) ? L - 1 : j - 1;
     const int jp = (j == L - 1) ? 0 : j + 1;
@@ -1282,16 +1370,15 @@ __global__ void __launch_bounds__(kBlock)
     s1 += x;
     s2 += x * x;
   }
-  block_sum3(sf, s1, s2, lds);
-  if (threadIdx.x == 0) part[tile] = Partial{sf, s1, s2, K};
+  emit<MODE>(t, o, w, len, sf, s1, s2, K, lds);
 }
 
-template <int KIND>
-__global__ void __launch_bounds__(kBlock) k_meas_split(Tables t, SplitBuf b, Phys ph, Partial* part) {
-  __shared__ double lds[3 * (kBlock / 64)];
-  const int tile = blockIdx.x;
-  const int s = t.mt_s[tile];
-  const int p0 = t.mt_p0[tile], len = t.mt_len[tile];
+template <int KIND, int MODE>
+__global__ void __launch_bounds__(meas_block(MODE)) k_meas_split(Tables t, SplitBuf b, Phys ph, MeasOut o) {
+  __shared__ MeasLds lds;
+  const TileOf w = tile_of<MODE>(t);
+  const int s = w.s;
+  const int p0 = w.valid ? t.mt_p0[w.tile] : 0, len = w.valid ? t.mt_len[w.tile] : 0;
   const int L = t.L[s];
   const int64_t base = t.off[s];
   const uint32_t id = t.did[s];
@@ -1301,7 +1388,7 @@ __global__ void __launch_bounds__(kBlock) k_meas_split(Tables t, SplitBuf b, Phy
   const double Kr = (double)b.frac[base + p0];
   const VectorKeys keys = vector_keys(ph.k0, ph.k1);
   double sf = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int q = threadIdx.x; q < len; q += kBlock) {
+  for (int q = w.tid; q < len; q += kBlock) {
     const int j = p0 + q;
     const int jm = (j == 0) ? L - 1 : j - 1;
     const int jp = (j == L - 1) ? 0 : j + 1;
@@ -1325,44 +1412,18 @@ __global__ void __launch_bounds__(kBlock) k_meas_split(Tables t, SplitBuf b, Phy
     s1 += x;
     s2 += x * x;
   }
-  block_sum3(sf, s1, s2, lds);
-  if (threadIdx.x == 0) part[tile] = Partial{sf, s1, s2, (double)Kc + Kr};
+  emit<MODE>(t, o, w, len, sf, s1, s2, (double)Kc + Kr, lds);
 }
 
-// Per-sample combine of tile partials: mean and sum of squared deviations by
-// the pairwise update of Chan, Golub and LeVeque, in a fixed order.
-struct Moments {
-  double n, mean, m2, sf;
-};
-
-__device__ __forceinline__ Moments combine(const Moments& a, const Moments& b) {
-  if (a.n == 0.0) return b;
-  if (b.n == 0.0) return a;
-  const double n = a.n + b.n;
-  const double d = b.mean - a.mean;
-  Moments r;
-  r.n = n;
-  r.mean = a.mean + d * (b.n / n);
-  r.m2 = (a.m2 + b.m2) + d * d * (a.n * b.n / n);
-  r.sf = a.sf + b.sf;
-  return r;
-}
-
+// Per-sample combine of tile partials (more than kFinalTiles of them).
 __global__ void __launch_bounds__(kBlock)
-    k_meas_final(Tables t, const Partial* part, int meas_index, int n_meas, double* series, double* v_host) {
+    k_meas_final(Tables t, MeasOut o) {
   __shared__ Moments lds[kBlock];
   const int s = blockIdx.x;
   const int t0 = t.mt_first[s], t1 = t.mt_first[s + 1];
   Moments acc{0.0, 0.0, 0.0, 0.0};
   for (int ti = t0 + threadIdx.x; ti < t1; ti += kBlock) {
-    const Partial p = part[ti];
-    const double n = (double)t.mt_len[ti];
-    Moments m;
-    m.n = n;
-    m.mean = p.shift + p.s1 / n;
-    m.m2 = p.s2 - p.s1 * (p.s1 / n);
-    m.sf = p.sum_f;
-    acc = combine(acc, m);
+    acc = combine(acc, moments_of(o.part[ti], t.mt_len[ti]));
   }
   lds[threadIdx.x] = acc;
   __syncthreads();
@@ -1370,16 +1431,7 @@ __global__ void __launch_bounds__(kBlock)
     if ((int)threadIdx.x < stride) lds[threadIdx.x] = combine(lds[threadIdx.x], lds[threadIdx.x + stride]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const Moments m = lds[0];
-    const double L = (double)t.L[s];
-    double* out = series + ((int64_t)s * n_meas + meas_index) * 3;
-    const double v = m.sf / L;
-    out[0] = v;
-    if (v_host) v_host[s] = v;  // pinned host memory
-    out[1] = m.mean;
-    out[2] = (m.m2 > 0.0 ? m.m2 : 0.0) / L;
-  }
+  if (threadIdx.x == 0) write_series(t, o, s, lds[0]);
 }
 
 // Disorder average over samples of one measurement index per workgroup:
@@ -1512,20 +1564,28 @@ hipError_t launch_refresh_nodes(const Tables& t, SplitBuf b, const Phys& ph, int
   return hipGetLastError();
 }
 
+// Launch KERNEL (a template on its measuring mode) as `o` asks.
+#define QEW_MEAS_LAUNCH(o, NONE, PARTIALS, FINAL, ...)                                                                  \
+  do {                                                                                                                  \
+    if ((o).groups > 0) hipLaunchKernelGGL(FINAL, dim3((o).n_samples), dim3(kBlock * (o).groups), 0, st, __VA_ARGS__);  \
+    else if ((o).part) hipLaunchKernelGGL(PARTIALS, dim3(t.n_mt), dim3(kBlock), 0, st, __VA_ARGS__);                    \
+    else hipLaunchKernelGGL(NONE, dim3(t.n_mt), dim3(kBlock), 0, st, __VA_ARGS__);                                      \
+  } while (0)
+
 template <int KIND>
 static void launch_plain_kind(const Tables& t, const double* uin, double* uout, const Phys& ph,
-                              Partial* part, hipStream_t st) {
-  if (part) hipLaunchKernelGGL((k_step_plain<KIND, true>), dim3(t.n_mt), dim3(kBlock), 0, st, t, uin, uout, ph, part);
-  else hipLaunchKernelGGL((k_step_plain<KIND, false>), dim3(t.n_mt), dim3(kBlock), 0, st, t, uin, uout, ph, part);
+                              const MeasOut& o, hipStream_t st) {
+  QEW_MEAS_LAUNCH(o, (k_step_plain<KIND, kNoMeas>), (k_step_plain<KIND, kPartials>), (k_step_plain<KIND, kFinal>), t,
+                  uin, uout, ph, o);
 }
 
 hipError_t launch_step_plain(const Tables& t, const double* uin, double* uout, const Phys& ph,
-                             int kind, Partial* part, hipStream_t st) {
+                             int kind, const MeasOut& o, hipStream_t st) {
   switch (kind) {
-    case kRF: launch_plain_kind<kRF>(t, uin, uout, ph, part, st); break;
-    case kRB: launch_plain_kind<kRB>(t, uin, uout, ph, part, st); break;
-    case kRBLin: launch_plain_kind<kRBLin>(t, uin, uout, ph, part, st); break;
-    default: launch_plain_kind<kRFPc>(t, uin, uout, ph, part, st); break;
+    case kRF: launch_plain_kind<kRF>(t, uin, uout, ph, o, st); break;
+    case kRB: launch_plain_kind<kRB>(t, uin, uout, ph, o, st); break;
+    case kRBLin: launch_plain_kind<kRBLin>(t, uin, uout, ph, o, st); break;
+    default: launch_plain_kind<kRFPc>(t, uin, uout, ph, o, st); break;
   }
   return hipGetLastError();
 }
@@ -1553,18 +1613,18 @@ hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout
 
 template <int KIND>
 static void launch_split1_kind(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph,
-                               Partial* part, hipStream_t st) {
-  if (part) hipLaunchKernelGGL((k_step_split1<KIND, true>), dim3(t.n_mt), dim3(kBlock), 0, st, t, in, out, ph, part);
-  else hipLaunchKernelGGL((k_step_split1<KIND, false>), dim3(t.n_mt), dim3(kBlock), 0, st, t, in, out, ph, part);
+                               const MeasOut& o, hipStream_t st) {
+  QEW_MEAS_LAUNCH(o, (k_step_split1<KIND, kNoMeas>), (k_step_split1<KIND, kPartials>), (k_step_split1<KIND, kFinal>), t,
+                  in, out, ph, o);
 }
 
 hipError_t launch_step_split1(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
-                              Partial* part, hipStream_t st) {
+                              const MeasOut& o, hipStream_t st) {
   switch (kind) {
-    case kRF: launch_split1_kind<kRF>(t, in, out, ph, part, st); break;
-    case kRB: launch_split1_kind<kRB>(t, in, out, ph, part, st); break;
-    case kRBLin: launch_split1_kind<kRBLin>(t, in, out, ph, part, st); break;
-    default: launch_split1_kind<kRFPc>(t, in, out, ph, part, st); break;
+    case kRF: launch_split1_kind<kRF>(t, in, out, ph, o, st); break;
+    case kRB: launch_split1_kind<kRB>(t, in, out, ph, o, st); break;
+    case kRBLin: launch_split1_kind<kRBLin>(t, in, out, ph, o, st); break;
+    default: launch_split1_kind<kRFPc>(t, in, out, ph, o, st); break;
   }
   return hipGetLastError();
 }
@@ -1641,22 +1701,42 @@ hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const P
   return hipGetLastError();
 }
 
+template <int KIND>
+static void launch_meas_plain_kind(const Tables& t, const double* u, const Phys& ph, const MeasOut& o, hipStream_t st) {
+  QEW_MEAS_LAUNCH(o, (k_meas_plain<KIND, kPartials>), (k_meas_plain<KIND, kPartials>), (k_meas_plain<KIND, kFinal>), t, u,
+                  ph, o);
+}
+
 hipError_t launch_meas_plain(const Tables& t, const double* u, const Phys& ph, int kind,
-                             Partial* part, hipStream_t st) {
-  QEW_KIND_DISPATCH(kind, k_meas_plain, dim3(t.n_mt), dim3(kBlock), 0, st, t, u, ph, part);
+                             const MeasOut& o, hipStream_t st) {
+  switch (kind) {
+    case kRF: launch_meas_plain_kind<kRF>(t, u, ph, o, st); break;
+    case kRB: launch_meas_plain_kind<kRB>(t, u, ph, o, st); break;
+    case kRBLin: launch_meas_plain_kind<kRBLin>(t, u, ph, o, st); break;
+    default: launch_meas_plain_kind<kRFPc>(t, u, ph, o, st); break;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int kind, Partial* part,
+template <int KIND>
+static void launch_meas_split_kind(const Tables& t, SplitBuf b, const Phys& ph, const MeasOut& o, hipStream_t st) {
+  QEW_MEAS_LAUNCH(o, (k_meas_split<KIND, kPartials>), (k_meas_split<KIND, kPartials>), (k_meas_split<KIND, kFinal>), t, b,
+                  ph, o);
+}
+
+hipError_t launch_meas_split(const Tables& t, SplitBuf b, const Phys& ph, int kind, const MeasOut& o,
                              hipStream_t st) {
-  QEW_KIND_DISPATCH(kind, k_meas_split, dim3(t.n_mt), dim3(kBlock), 0, st, t, b, ph, part);
+  switch (kind) {
+    case kRF: launch_meas_split_kind<kRF>(t, b, ph, o, st); break;
+    case kRB: launch_meas_split_kind<kRB>(t, b, ph, o, st); break;
+    case kRBLin: launch_meas_split_kind<kRBLin>(t, b, ph, o, st); break;
+    default: launch_meas_split_kind<kRFPc>(t, b, ph, o, st); break;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_meas_final(const Tables& t, int n_samples, const Partial* part, int meas_index,
-                             int n_meas, double* series, double* v_host, hipStream_t st) {
-  hipLaunchKernelGGL(k_meas_final, dim3(n_samples), dim3(kBlock), 0, st, t, part, meas_index, n_meas,
-                     series, v_host);
+hipError_t launch_meas_final(const Tables& t, const MeasOut& o, hipStream_t st) {
+  hipLaunchKernelGGL(k_meas_final, dim3(o.n_samples), dim3(kBlock), 0, st, t, o);
   return hipGetLastError();
 }
 

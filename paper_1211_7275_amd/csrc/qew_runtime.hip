@@ -116,6 +116,7 @@ struct qew_plan_s {
   int64_t padded = 0, total_sites = 0;
   std::vector<int32_t> mt_s, mt_p0, mt_len, mt_first;
   std::vector<int32_t> ft_s, ft_p0, ft_len;
+  int32_t meas_groups = 0;  // measurement tiles of a sample one workgroup takes (0: one each)
   int32_t ft_capacity = 0;
   int32_t k = 1, tile = 0, autotuned = 0;
   int32_t bk = 0, btile = 0;  // FP64 path: steps per blocked launch (0: one-step launches only) and its tile
@@ -440,21 +441,35 @@ qew_status init_state(qew_plan_t* p, void* ws, hipStream_t st) {
   return QEW_OK;
 }
 
-Partial* partials_of(const qew_plan_t* p, void* ws) {
-  return reinterpret_cast<Partial*>(small_of(p, ws) + p->lay.part);
+// Whether the run follows the line's velocity (choose_variant).
+bool follows_velocity(const qew_plan_t* p) {
+  return fused(p) && !lanes(p) && !p->direct_only && !(p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE));
+}
+
+// Destination of measurement mi.
+MeasOut measure_to(const qew_plan_t* p, void* ws, int mi) {
+  MeasOut o;
+  o.part = reinterpret_cast<Partial*>(small_of(p, ws) + p->lay.part);
+  o.series = series_of(p, ws);
+  o.v_host = follows_velocity(p) ? p->rb_host + (size_t)p->rb_next * p->S : nullptr;
+  o.mi = mi;
+  o.n_meas = (int32_t)p->meas.size();
+  o.n_samples = p->S;
+  o.groups = p->meas_groups;
+  return o;
 }
 
 // One Euler step from buffer `from` with the one-step kernel of the plan's
-// precision (the split one-step kernel on the fused path); with `part`
-// non-null it also writes the measurement partials of the state it reads.
-hipError_t onestep_launch(const qew_plan_t* p, void* ws, int from, Partial* part, hipStream_t st) {
+// precision (the split one-step kernel on the fused path); with o.part
+// non-null it also measures the state it reads.
+hipError_t onestep_launch(const qew_plan_t* p, void* ws, int from, const MeasOut& o, hipStream_t st) {
   const Tables t = tables_of(p, ws);
   const Phys ph = phys_of(p);
   if (p->precision == QEW_FP64_PLAIN)
-    return launch_step_plain(t, plain_buf(p, ws, from), plain_buf(p, ws, from ^ 1), ph, p->kind, part, st);
+    return launch_step_plain(t, plain_buf(p, ws, from), plain_buf(p, ws, from ^ 1), ph, p->kind, o, st);
   SplitBuf in = split_buf(p, ws, from), out = split_buf(p, ws, from ^ 1);
   in.nodes = out.nodes = nullptr;  // the one-step kernel regenerates nodes
-  return launch_step_split1(t, in, out, ph, p->kind, part, st);
+  return launch_step_split1(t, in, out, ph, p->kind, o, st);
 }
 
 // One launch of the fused kernel: nsub Euler steps from buffer `from`.
@@ -474,7 +489,7 @@ hipError_t step_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipStr
   if (nsub > 1)
     return launch_blocked_plain(tables_of(p, ws), plain_buf(p, ws, from), plain_buf(p, ws, from ^ 1), phys_of(p),
                                 p->kind, p->btile, p->bk, nsub, st);
-  return onestep_launch(p, ws, from, nullptr, st);
+  return onestep_launch(p, ws, from, MeasOut{}, st);
 }
 
 qew_status ensure_fused_grid(qew_plan_t* p) {
@@ -581,11 +596,11 @@ qew_status advance(qew_plan_t* p, void* ws, int64_t n, hipStream_t st) {
 }
 
 // n Euler steps with the one-step kernel on the fused path (short stretches);
-// the first one also writes the measurement partials when `part` is given.
+// the first one also measures when o.part is given.
 // The node cache no longer matches the state afterwards.
-qew_status advance_onestep(qew_plan_t* p, void* ws, int64_t n, Partial* part, hipStream_t st) {
+qew_status advance_onestep(qew_plan_t* p, void* ws, int64_t n, const MeasOut& o, hipStream_t st) {
   for (int64_t i = 0; i < n; ++i) {
-    QEW_HIP(onestep_launch(p, ws, p->cur_buf, i == 0 ? part : nullptr, st));
+    QEW_HIP(onestep_launch(p, ws, p->cur_buf, i == 0 ? o : MeasOut{}, st));
     p->cur_buf ^= 1;
     count_launches(p, 1, false);
   }
@@ -615,11 +630,6 @@ qew_status choose_variant(qew_plan_t* p) {
   return QEW_OK;
 }
 
-// Whether the run follows the line's velocity (choose_variant).
-bool follows_velocity(const qew_plan_t* p) {
-  return fused(p) && !lanes(p) && !p->direct_only && !(p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE));
-}
-
 // After a measurement whose last kernel wrote the velocities of every sample
 // into the next slot of rb_host: mark when they are there.  (A copy of them
 // from the device series, 8 bytes per sample at a stride, held the stream for
@@ -632,15 +642,13 @@ qew_status post_velocities(qew_plan_t* p, hipStream_t st) {
   return QEW_OK;
 }
 
-// Measurement mi of the state in buffer `buf`, from the tile partials already
-// written (by the measurement kernels or by a one-step launch that also
-// measured): per-sample v, ubar, w2 into the series, and the structure
-// factor when the problem asks for it.
+// The rest of measurement mi of the state in buffer `buf`, which the measurement
+// kernels or a one-step launch have measured: the tile partials, where there
+// are any, to per-sample v, ubar, w2 in the series, and the structure factor
+// when the problem asks for it.
 qew_status measure_finish(qew_plan_t* p, void* ws, int mi, int buf, hipStream_t st) {
   const Tables t = tables_of(p, ws);
-  double* series = series_of(p, ws);
-  QEW_HIP(launch_meas_final(t, p->S, partials_of(p, ws), mi, (int)p->meas.size(), series,
-                            follows_velocity(p) ? p->rb_host + (size_t)p->rb_next * p->S : nullptr, st));
+  if (p->meas_groups == 0) QEW_HIP(launch_meas_final(t, measure_to(p, ws, mi), st));
   if (p->sq_bins > 0) {
     char* b = static_cast<char*>(ws);
     const bool plain = p->precision == QEW_FP64_PLAIN;
@@ -662,11 +670,11 @@ qew_status measure(qew_plan_t* p, void* ws, int mi, hipStream_t st) {
   const Tables t = tables_of(p, ws);
   const Phys ph = phys_of(p);
   if (p->precision == QEW_FP64_PLAIN) {
-    QEW_HIP(launch_meas_plain(t, plain_buf(p, ws, p->cur_buf), ph, p->kind, partials_of(p, ws), st));
+    QEW_HIP(launch_meas_plain(t, plain_buf(p, ws, p->cur_buf), ph, p->kind, measure_to(p, ws, mi), st));
   } else {
     SplitBuf b = split_buf(p, ws, p->cur_buf);
     if (!(fused(p) && p->nodes_valid)) b.nodes = nullptr;
-    QEW_HIP(launch_meas_split(t, b, ph, p->kind, partials_of(p, ws), st));
+    QEW_HIP(launch_meas_split(t, b, ph, p->kind, measure_to(p, ws, mi), st));
   }
   return measure_finish(p, ws, mi, p->cur_buf, st);
 }
@@ -817,6 +825,9 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
     p->mt_first.push_back((int32_t)p->mt_s.size());
   }
   p->padded = o;
+  int32_t most = 0;  // measurement tiles of the longest chain
+  for (int32_t s = 0; s < p->S; ++s) most = std::max(most, p->mt_first[s + 1] - p->mt_first[s]);
+  p->meas_groups = most > kFinalTiles ? 0 : most;
   if (p->mt_s.size() > (size_t)INT32_MAX / 2) {
     delete p;
     return fail(QEW_EINVAL, "too many sites");
@@ -1051,7 +1062,7 @@ static qew_status run_impl(qew_plan_t* p, void* ws, size_t bytes, hipStream_t st
       if (onestep) {
         const int from = p->cur_buf;
         if ((he = open_step(false)) != hipSuccess) break;
-        if ((rc = advance_onestep(p, ws, 1, partials_of(p, ws), st)) != QEW_OK) break;
+        if ((rc = advance_onestep(p, ws, 1, measure_to(p, ws, mi), st)) != QEW_OK) break;
         if ((he = close_ev(step_ev)) != hipSuccess) break;
         if ((he = open_ev(meas_ev)) != hipSuccess) break;
         if ((rc = measure_finish(p, ws, mi, from, st)) != QEW_OK) break;
@@ -1067,7 +1078,7 @@ static qew_status run_impl(qew_plan_t* p, void* ws, size_t bytes, hipStream_t st
     }
     if (n > 0 && onestep) {
       if ((he = open_step(false)) != hipSuccess) break;
-      if (fused(p)) rc = advance_onestep(p, ws, n, nullptr, st);
+      if (fused(p)) rc = advance_onestep(p, ws, n, MeasOut{}, st);
       else rc = advance(p, ws, n, st);
       if (rc != QEW_OK) break;
       if ((he = close_ev(step_ev)) != hipSuccess) break;

@@ -70,7 +70,7 @@ hipError_t launch_step_plain(const Tables& t, const double* uin, double* uout, c
                              int kind, const MeasOut& o, hipStream_t st);
 // nsub <= halo Euler steps of the FP64 state on the tiles of the list ft_* (T = `tile`
 // sites per workgroup: 512 or 256 for small problems, else blocked_wide_tile(kind)).
-constexpr int blocked_wide_tile(int kind) { return kind == 1 ? 1024 : 2048; }
+constexpr int blocked_wide_tile(int kind) { return kind == 1 ? 1024 : 1536; }
 hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout, const Phys& ph, int kind,
                                 int tile, int halo, int nsub, hipStream_t st);
 hipError_t launch_step_split1(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,

@@ -751,11 +751,16 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
 //
 // Bound by VALU issue: 16 FP64 operations of 4 cycles per site and step (some
 // 10 us per step at 2^22 x 4), 6 to post a site's cell change, and a service
-// pass of some 90 instructions per wave and sub-step, whose 64 lanes about 22
-// requests of a wave's 512 sites fill to a third.  2048-site tiles at k = 64:
-// 25.3 us per step against 97 of the one-step kernel (3072-site tiles 28.0,
-// 1024-site 29.2: registers and LDS for fewer waves, the pass shared by fewer
-// sites); a launch costs 110 us more for loads and the nodes of its tiles.
+// pass of some 90 instructions per wave and sub-step, whose 64 lanes about 17
+// requests of a wave's 384 sites fill to a quarter.  A launch costs 110 us more
+// for loads and the nodes of its tiles.  1536 sites are what lets four waves
+// per SIMD have their registers and LDS, and leave a wave's request region room
+// on fast lines.  us per step at 2^22 x 4, k = 64 (one step per launch: 97):
+//                                      1536 sites  2048 sites
+//   RF, f = 0.5 / 1.0 / 2.4          23.2 / 25.2 / 27.1  23.7 / 25.6 / 33.5
+//   RB linear, the same drives       66.0 / 63.0 / 37.4  88.2 / 79.8 / 43.2
+//   RF without interpolation         53.9 / 31.5 / 31.3  62.3 / 46.3 / 41.3
+// (RF, f = 1: 3072 sites 28.0, 1024 sites 29.2; k = 48 to 96 within 3 %.)
 // Random bond, whose windows take twice the LDS, on 1024-site tiles: 42
 // against 406 us.
 //
@@ -856,9 +861,10 @@ __device__ __forceinline__ double from_upper_lane(double x) {
   return __longlong_as_double(((uint64_t)hi << 32) | lo);
 }
 
-// Waves per SIMD the register allocation must allow (the Box-Muller transform
-// of the Gaussian kinds needs more registers).
-constexpr int blocked_min_waves(int kind) { return kind == kRF || kind == kRB ? 3 : 2; }
+// Waves per SIMD the register allocation must allow.  Random bond: no more fit
+// the LDS.  Linear random bond: the Box-Muller transform and its windows spill
+// at four (107 us per step at 2^22 x 4 against 63).
+constexpr int blocked_min_waves(int kind) { return kind == kRF || kind == kRFPc ? 4 : 3; }
 
 template <int KIND, int P>
 __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
@@ -1594,7 +1600,7 @@ template <int KIND>
 static void launch_blocked_kind(const Tables& t, const double* uin, double* uout, const Phys& ph, int tile,
                                 int halo, int nsub, hipStream_t st) {
   const dim3 g(t.n_ft), b(kBlock);
-  constexpr int wide = KIND == kRB ? 4 : 8;
+  constexpr int wide = blocked_wide_tile(KIND) / kBlock;
   if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 1>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
   else if (tile == 512) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
   else hipLaunchKernelGGL((k_blocked_plain<KIND, wide>), g, b, 0, st, t, uin, uout, ph, halo, nsub);

@@ -177,10 +177,10 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
 // tried in order, each taken if it needs at most `most` workgroups.  Measured,
 // us per step (RF, four chains of L; last column: the tuner's wide tiles):
 //                256/112  256/96  256/64  512/64   wide
-//   L = 2^10       0.33     0.34    0.38    0.57   0.92
-//   L = 2^14       0.68     0.46    0.40    0.59   0.83
-//   L = 2^16       2.1      1.2     0.75    0.70   0.88
-//   L = 2^17       4.1      2.1     1.23    1.02   0.97
+//   L = 2^10       0.32     0.33    0.35    0.58   0.93
+//   L = 2^14       0.67     0.43    0.36    0.59   0.82
+//   L = 2^16       2.03     1.12    0.69    0.67   0.86
+//   L = 2^17       3.84     2.03    1.16    1.01   0.96
 bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   if (!fused(p) || p->k_req || p->tile_req || (p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
   struct { int tile, k; int64_t most; } const geometry[] = {{256, 112, 256}, {256, 96, 256}, {256, 64, 1024}, {512, 64, 1152}};
@@ -197,11 +197,11 @@ bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
 // runs at the memory's rate one step at a time).  The candidates are tried in
 // order, each taken if it needs at most `most` workgroups.  Measured, us per
 // step (RF, four chains of L):
-//                      256/112  256/96  256/64  512/64  2048/64
-//   L = 2^10             0.37     0.37    0.40    0.62
-//   L = 2^14             0.98     0.63    0.47    0.63
-//   L = 2^16             3.2      1.7     1.05    0.91
-//   L = 2^18                      6.3     3.3     2.34    2.39
+//                      256/112  256/96  256/64  512/64  1536/64
+//   L = 2^10             0.35     0.36    0.39    0.62
+//   L = 2^14             0.94     0.58    0.44    0.61
+//   L = 2^16             3.05     1.65    0.97    0.88
+//   L = 2^18            11.5      5.9     3.15    2.28    2.39
 //   L = 2^22                                              25.3   (one step per launch: 97)
 void build_blocked_tiles(qew_plan_t* p) {
   if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;

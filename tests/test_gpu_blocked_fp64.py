@@ -46,6 +46,22 @@ def test_blocked_fp64_matches_oracle(kind, L, samples, steps):
         assert np.max(np.abs(out["ubar"][s] - ref["ubar"])) <= 1e-10
 
 
+@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+@pytest.mark.parametrize("L", [9856 * 86 - 1, 9856 * 86, 9856 * 86 + 1])
+def test_wide_tile_edges(kind, L):
+    """Wide tiles (1408 and 896 valid sites) whose last one is full, short of one
+    site, or a single site; the second launch takes two steps."""
+    from oracle import oracle
+    from paper_1211_7275_amd import qew
+    steps = 66
+    start = [np.cumsum(np.random.default_rng(L + kind).normal(0.0, 0.7, L))]
+    p = workloads.custom(kind, [L], 2.4, steps, [0], SEED + 2)
+    print("[gpu-test] blocked FP64 tile edges, kind", kind, "L", L, flush=True)
+    _, u = _run(qew, p, start)
+    ref = oracle.run_sample(kind, 1.0, SEED + 2, 0, L, 1.0, 0.05, 2.4, steps, [], u0=start[0])
+    assert np.max(np.abs(u[0] - ref["u"])) <= 1e-10
+
+
 @pytest.mark.parametrize("L", [130, 1001, 40_007, 1_000_003])
 def test_every_site_changes_cell_at_once(L):
     """A line that advances one cell in every step (more requests than a wave's

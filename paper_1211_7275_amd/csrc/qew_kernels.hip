@@ -1601,9 +1601,10 @@ static void launch_blocked_kind(const Tables& t, const double* uin, double* uout
                                 int halo, int nsub, hipStream_t st) {
   const dim3 g(t.n_ft), b(kBlock);
   constexpr int wide = blocked_wide_tile(KIND) / kBlock;
-  if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 1>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
-  else if (tile == 512) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
-  else hipLaunchKernelGGL((k_blocked_plain<KIND, wide>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  if (tile == wide * kBlock) hipLaunchKernelGGL((k_blocked_plain<KIND, wide>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  else if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 1>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  else if constexpr (KIND < kRBLin)  // 512, which the rule takes for the spline kinds only
+    hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
 }
 
 hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout, const Phys& ph, int kind,
@@ -1677,7 +1678,8 @@ static void launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const 
   if constexpr (!SPARSE) {
     if (tile == 256 || tile == 512) {  // one workgroup per tile
       if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 1>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
-      else hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 2>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
+      else if constexpr (KIND < kRBLin)  // 512, which the rule takes for the spline kinds only
+        hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 2>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
       return;
     }
   }

@@ -181,9 +181,15 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
 //   L = 2^14       0.67     0.43    0.36    0.59   0.82
 //   L = 2^16       2.03     1.12    0.69    0.67   0.86
 //   L = 2^17       3.84     2.03    1.16    1.01   0.96
+// The kinds whose force jumps make sites hop between two cells, and a step back
+// has no node ready, so narrow tiles lose early: linear random bond, f = 0.8, at
+// 2^13 0.95 against 1.90 wide, at 2^16 3.3 against 1.85; without interpolation
+// 1.01 against 0.98 and 3.3 against 1.06.
 bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   if (!fused(p) || p->k_req || p->tile_req || (p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
-  struct { int tile, k; int64_t most; } const geometry[] = {{256, 112, 256}, {256, 96, 256}, {256, 64, 1024}, {512, 64, 1152}};
+  const bool hops = p->kind >= 2;
+  struct { int tile, k; int64_t most; } const geometry[] = {
+      {256, 112, 256}, {256, 96, 256}, {256, 64, hops ? 256 : 1024}, {512, 64, hops ? 0 : 1152}};
   for (const auto& g : geometry) {
     if (fused_tile_count(p, g.tile, g.k) > g.most) continue;
     *tile = g.tile;
@@ -201,12 +207,21 @@ bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
 //   L = 2^10             0.35     0.36    0.39    0.62
 //   L = 2^14             0.94     0.58    0.44    0.61
 //   L = 2^16             3.05     1.65    0.97    0.88
-//   L = 2^18            11.5      5.9     3.15    2.28    2.39
-//   L = 2^22                                              25.3   (one step per launch: 97)
+//   L = 2^18            11.5      5.9     3.15    2.28    2.01
+//   L = 2^22                                              25.2   (one step per launch: 97)
+// Random bond, 512/64 against wide (f = 1.0 / 2.4): at 2^18 2.6 / 4.6 against
+// 3.5 / 4.5, at 2^22 31 / 63 against 42 / 59.  The kinds whose force jumps (f =
+// 0.8): linear random bond 256/64 at 2^13 1.84, at 2^14 2.87, 512/64 at 2^16 8.0
+// against 2.84 wide at any of them; without interpolation at 2^14 1.98 (256/64),
+// at 2^16 5.4 (512/64) against 2.4 wide.
 void build_blocked_tiles(qew_plan_t* p) {
   if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
-  struct { int tile, k; int64_t most; } const geometry[] = {
-      {256, 112, 256}, {256, 96, 256}, {256, 64, 1024}, {512, 64, 2048}, {blocked_wide_tile(p->kind), 64, INT64_MAX}};
+  const int64_t most_64[4] = {1024, 1024, 256, 512}, most_512[4] = {2048, 4096, 0, 0};
+  struct { int tile, k; int64_t most; } const geometry[] = {{256, 112, 256},
+                                                            {256, 96, 256},
+                                                            {256, 64, most_64[p->kind]},
+                                                            {512, 64, most_512[p->kind]},
+                                                            {blocked_wide_tile(p->kind), 64, INT64_MAX}};
   if (fused_tile_count(p, 256, 112) > INT32_MAX / 2 &&
       fused_tile_count(p, geometry[4].tile, geometry[4].k) > INT32_MAX / 2)
     return;

@@ -35,7 +35,8 @@ def _same(a, b):
         assert np.array_equal(a[key], b[key], equal_nan=True), key
 
 
-# (lengths, the tile the size rule takes): one, a few and many workgroups per CU, and the timed tiles
+# (lengths, the tile the size rule takes; kinds 2 and 3 go from 256 to the timed tiles): one, a few
+# and many workgroups per CU, and the timed tiles
 SHAPES = [([3, 4, 5], 256), ([130, 1001, 255], 256), ([9001] * 3, 256), ([40_007] * 4, 512),
           ([100_003] * 3, 512), ([700_001], 0)]
 
@@ -51,6 +52,8 @@ def test_narrow_tiles_match_one_step(kind, L, tile):
     p = workloads.custom(kind, L, 2.1, 260, [0, 1, 5, 9, 100, 260], SEED, strength=0.8, period=11)
     print("[gpu-test] narrow tiles kind", kind, "L", L, flush=True)
     got, info = _run(qew, p, qew.QEW_FUSED, start)
+    if tile == 512 and kind >= 2:
+        tile = 0
     assert info.tile == tile if tile else info.tile >= 1024
     ref, _ = _run(qew, p, qew.QEW_ONE_STEP, start)
     _same(got, ref)

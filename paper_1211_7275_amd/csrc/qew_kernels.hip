@@ -56,6 +56,14 @@ __device__ __forceinline__ float from_upper_lane(float x) {
 // A pointer into LDS (32-bit, address space 3).
 typedef __attribute__((address_space(3))) float lds_f32;
 
+// Between two rounds of the request slots of a wave: no lane's next request may
+// be written before every lane has read its reply from the slot.  The wave's LDS
+// operations complete in program order, so only the compiler has to keep it.
+__device__ __forceinline__ void slots_read() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -641,6 +649,7 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
       if constexpr (P <= 8) {
 #pragma unroll 1
         for (uint32_t done = RQ; done < nreq; done += RQ) {
+          slots_read();
           uint32_t first = 0u;
           bool mine[P];
 #pragma unroll
@@ -659,7 +668,6 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
 #pragma unroll
           for (int i = 0; i < P; ++i)
             if (mine[i]) read_back(i, kb[i]);
-          __builtin_amdgcn_wave_barrier();
         }
       } else if (nreq > (uint32_t)RQ) {
 #pragma unroll
@@ -876,10 +884,14 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
   constexpr int NC = CoefD<KIND>::N;
   using Win = WindowD<KIND>;
   // A request: the new cell and the site's index; its reply: the coefficients.
+  // Every access to a slot goes through these types: it holds a cell and an index
+  // first and four coefficients later, and the order of the two must hold.
+  typedef double __attribute__((may_alias)) slot_f64;
+  typedef int __attribute__((may_alias)) slot_i32;
   struct __align__(16) Req {
-    double cell;
-    int site, pad;
-    double more[2];
+    slot_f64 cell;
+    slot_i32 site, pad;
+    slot_f64 more[2];
   };
   __shared__ __align__(16) Win s_win[T];  // nodes of the site's cell, slot-major
   __shared__ int s_cell[T];
@@ -1026,7 +1038,7 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
           s_win[ni] = w;
           s_cell[ni] = n;
           const CoefD<KIND> c = w.coef(str, unit);
-          double* reply = reinterpret_cast<double*>(rq);
+          slot_f64* reply = reinterpret_cast<slot_f64*>(rq);
 #pragma unroll
           for (int q = 0; q < NC; ++q) reply[q] = c.a[q];
         }
@@ -1034,7 +1046,7 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
         __builtin_amdgcn_wave_barrier();
       };
       auto read_back = [&](int i, uint32_t at) {
-        const double* reply = reinterpret_cast<const double*>(reinterpret_cast<const char*>(s_req) + at);
+        const slot_f64* reply = reinterpret_cast<const slot_f64*>(reinterpret_cast<const char*>(s_req) + at);
 #pragma unroll
         for (int q = 0; q < NC; ++q) a[i].a[q] = reply[q];
       };
@@ -1042,9 +1054,9 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
 #pragma unroll
       for (int i = 0; i < P; ++i)
         if (mv[i]) read_back(i, kb[i]);
-      __builtin_amdgcn_wave_barrier();
       // A burst of more cell changes than the region holds: further rounds.
       for (uint32_t done = RQ; done < nreq; done += RQ) {
+        slots_read();
         uint32_t first = 0u;
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -1061,7 +1073,6 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
 #pragma unroll
         for (int i = 0; i < P; ++i)
           if (mv[i] && kb[i] - rbase_b < (uint32_t)(RQ * sizeof(Req))) read_back(i, kb[i]);
-        __builtin_amdgcn_wave_barrier();
       }
     }
     __builtin_amdgcn_s_setprio(2);

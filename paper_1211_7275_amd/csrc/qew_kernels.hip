@@ -56,6 +56,10 @@ __device__ __forceinline__ float from_upper_lane(float x) {
 // A pointer into LDS (32-bit, address space 3).
 typedef __attribute__((address_space(3))) float lds_f32;
 
+// Node c + d of cell c.  Nodes are numbered modulo 2^32 (the generator's counter
+// word), so that the windows of the last cells go on past the largest integer.
+__device__ __forceinline__ int32_t node_after(int32_t c, int d) { return (int32_t)((uint32_t)c + (uint32_t)d); }
+
 // Between two rounds of the request slots of a wave: no lane's next request may
 // be written before every lane has read its reply from the slot.  The wave's LDS
 // operations complete in program order, so only the compiler has to keep it.
@@ -613,8 +617,9 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
             w4 = make_float4(node_f32<KIND>((uint32_t)j, cell - 1, id, ph.k0, ph.k1, ph.period), w4.x, w4.y, w4.z);
           } else {
 #pragma unroll 1
-            for (int m = cell - 1; m <= cell + 2; ++m)
-              w4 = make_float4(w4.y, w4.z, w4.w, node_f32<KIND>((uint32_t)j, m, id, ph.k0, ph.k1, ph.period));
+            for (int i = 0; i < 4; ++i)
+              w4 = make_float4(w4.y, w4.z, w4.w,
+                               node_f32<KIND>((uint32_t)j, node_after(cell, i - 1), id, ph.k0, ph.k1, ph.period));
           }
           s_nodes[ni] = w4;
           float4 co;
@@ -927,15 +932,14 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
   // node; all of them after a jump or at the start, move = 0).
   auto advance_window = [&](Win& w, int j, int32_t n, int move) {
     if (__all(move == 1)) {  // the usual case: every site of the wave moved forward by one
-      w.push_up(node_f64<KIND>((uint32_t)j, n + Win::kHigh, id, ph.k0, ph.k1, ph.period));
+      w.push_up(node_f64<KIND>((uint32_t)j, node_after(n, Win::kHigh), id, ph.k0, ph.k1, ph.period));
       return;
     }
     const bool down = move == -1;
-    int32_t m = move == 1 ? n + Win::kHigh : n + Win::kLow;
-    const int last = down ? m : n + Win::kHigh;
+    const int first = move == 1 ? Win::kHigh : Win::kLow, last = down ? first : Win::kHigh;
 #pragma unroll 1
-    for (; m <= last; ++m) {
-      const double x = node_f64<KIND>((uint32_t)j, m, id, ph.k0, ph.k1, ph.period);
+    for (int m = first; m <= last; ++m) {
+      const double x = node_f64<KIND>((uint32_t)j, node_after(n, m), id, ph.k0, ph.k1, ph.period);
       if (down) w.push_down(x);
       else w.push_up(x);
     }
@@ -1034,7 +1038,9 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
           const int ni = rq->site;
           const int32_t n = (int32_t)rq->cell;
           Win w = s_win[ni];
-          advance_window(w, column((int)(((uint32_t)ni % kBlock) * P + (uint32_t)ni / kBlock)), n, n - s_cell[ni]);
+          // Beyond the 32-bit cells all sites share the last one: no move, a whole window.
+          const int move = (int)((uint32_t)n - (uint32_t)s_cell[ni]);
+          advance_window(w, column((int)(((uint32_t)ni % kBlock) * P + (uint32_t)ni / kBlock)), n, move);
           s_win[ni] = w;
           s_cell[ni] = n;
           const CoefD<KIND> c = w.coef(str, unit);
@@ -1200,7 +1206,7 @@ struct LanesS {  // split state; the window comes from and returns to the node c
     x.r = in.frac[g];
     return (uint32_t)(d + (1 << 23)) >= (1u << 24);  // the difference must be exact in FP32
   }
-  static __device__ __forceinline__ int32_t cell(const Site& x, int32_t cbase) { return cbase + (int32_t)x.c; }
+  static __device__ __forceinline__ int32_t cell(const Site& x, int32_t cbase) { return node_after(cbase, (int32_t)x.c); }
   static __device__ __forceinline__ edge_t edge(const Site& x) { return {x.c, x.r}; }
   static __device__ __forceinline__ edge_t lower(const edge_t& e) { return {from_lower_lane(e.c), from_lower_lane(e.r)}; }
   static __device__ __forceinline__ edge_t upper(const edge_t& e) { return {from_upper_lane(e.c), from_upper_lane(e.r)}; }
@@ -1277,8 +1283,8 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
   auto fresh = [&](typename A::Site& y, int j) {
     const int32_t n = A::cell(y, cbase);
 #pragma unroll 1
-    for (int m = n + A::kHigh - (int)(sizeof(y.w.v) / sizeof(y.w.v[0])) + 1; m <= n + A::kHigh; ++m)
-      y.w.push_up(A::node((uint32_t)j, m, id, ph));
+    for (int m = A::kHigh + 1 - (int)(sizeof(y.w.v) / sizeof(y.w.v[0])); m <= A::kHigh; ++m)
+      y.w.push_up(A::node((uint32_t)j, node_after(n, m), id, ph));
   };
 #pragma unroll
   for (int i = 0; i < P; ++i) {
@@ -1319,7 +1325,7 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
       const bool up = d[i] == 1;
       if (__ballot(up && ahead[i] == 0) != 0u) {
         if (ahead[i] < kSpare) {
-          const int32_t m = A::cell(x[i], cbase) - (up ? 1 : 0) + A::kHigh + 1 + ahead[i];
+          const int32_t m = node_after(A::cell(x[i], cbase), (up ? A::kHigh : A::kHigh + 1) + ahead[i]);
           const node_t nd = A::node((uint32_t)col[i], m, id, ph);
           s_ahead[m & (kSpare - 1)][i * kBlock + tid] = nd;
           if (ahead[i] == 0) next[i] = nd;
@@ -1330,7 +1336,7 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
         x[i].w.push_up(next[i]);
         A::coef(x[i], k);
         ahead[i] -= 1;
-        next[i] = s_ahead[(A::cell(x[i], cbase) + A::kHigh + 1) & (kSpare - 1)][i * kBlock + tid];
+        next[i] = s_ahead[node_after(A::cell(x[i], cbase), A::kHigh + 1) & (kSpare - 1)][i * kBlock + tid];
       }
       const bool other = d[i] != 0 && !up;
       if (__ballot(other) != 0u) {  // rare: backwards, or more than one cell

@@ -44,3 +44,44 @@ def test_bursts_on_wide_tiles(kind, f):
     print("[gpu-test] FP64 bursts on wide tiles, kind", kind, "f", f, flush=True)
     start = [np.cumsum(np.random.default_rng(kind).normal(0.0, 0.5, L))]
     _same(qew, workloads.custom(kind, [L], f, 90, [0], SEED, strength=0.7), start)
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+@pytest.mark.parametrize("L", [203, 40_007, 1_800_001])
+@pytest.mark.parametrize("side", [1.0, -1.0])
+def test_last_cells(kind, L, side):
+    """Lines that reach the last 32-bit cells, whose windows go on past the largest
+    integer, and pass beyond them (all sites then share the last cell)."""
+    from paper_1211_7275_amd import qew
+    stride, steps = 2.0**26, 24
+    rng = np.random.default_rng(L + kind)
+    start = [side * (2.0**31 + rng.uniform(-7.0, 5.0, L) - 20 * stride)]  # at the limit after 20 steps
+    print("[gpu-test] last cells, FP64 kind", kind, "L", L, "side", side, flush=True)
+    _same(qew, workloads.custom(kind, [L], side * 20.0 * stride, steps, [0], SEED), start)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("L,k,tile", [(20_001, 0, 0), (200_003, 0, 0), (20_001, 24, 1024)])
+def test_last_cells_split(kind, L, k, tile):
+    """The same for the split state, whose cells count on past the limit: narrow
+    tiles of both widths and wide ones against one step per launch."""
+    from paper_1211_7275_amd import qew
+    stride, at_limit = 65536, 17_520  # cells per step, the step after which the line stands at the limit
+    steps = at_limit + 2
+    # 4000 cells of spread: sites stand in each of the last cells
+    start = 2.0**31 - at_limit * stride + 2000.0 * np.cos(2.0 * np.pi * np.arange(L) / L)
+    p = workloads.custom(kind, [L], 20.0 * stride, steps, [steps], SEED + 1)
+    print("[gpu-test] last cells, split kind", kind, "L", L, "k", k, flush=True)
+    got = []
+    for path, kk, tt in ((qew.QEW_FUSED, k, tile), (qew.QEW_ONE_STEP, 0, 0)):
+        sim = qew.Simulation(p, precision=qew.QEW_FP32_SPLIT, path=path, k=kk, tile=tt)
+        try:
+            if not kk:
+                sim.autotune()
+            sim.write_state(0, start, 0)
+            sim.run(resume=True)
+            got.append(sim.read_state(0)[0])
+        finally:
+            sim.close()
+    assert got[0].max() < 0.0  # past the last cell
+    assert np.array_equal(got[0], got[1])

@@ -391,6 +391,7 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
   constexpr int T = kBlock * P;
   constexpr int NW = kBlock / 64;
   constexpr int RQ = kReqPerWave;
+  constexpr bool kRounds = P <= 8 && !(SPARSE && KIND == kRF);  // how a burst of requests is served
   __shared__ float4 s_nodes[T];
   __shared__ int4 s_req[NW * (RQ + 1)];  // per wave: RQ requests, then one sink slot
   // End sites of each wave, double-buffered: [parity][cell, offset][slot][end],
@@ -646,12 +647,15 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
         __builtin_amdgcn_wave_barrier();
       }
       // Rare: more requests than the region holds (a burst of cell changes).
-      // Those past it are posted and served in further rounds; on tiles of 12
-      // or more sites per thread, where the rounds' code costs the common path
-      // 3 % (measured), their lanes make their windows themselves.  At
-      // 2^22 x 4 on 2048-site tiles, k = 56, ms per launch, that and the rounds:
+      // Those past it are posted and served in further rounds.  Where the rounds'
+      // code costs the common path more than it gives, their lanes make their
+      // windows themselves: tiles of 12 or more sites per thread (3 %), and the
+      // sparse random-field kernel, whose registers then allow a wave per SIMD
+      // less or spill (2^20 x 4, f = 0.8, us per step with rounds and without:
+      // 1024-site tiles 6.25, 4.80; 1536-site ones 4.84, 4.05).  At
+      // 2^22 x 4 on 2048-site tiles, k = 56, ms per launch, own windows and rounds:
       // f = 1.0 0.692, 0.678; f = 2.5 1.165, 1.042; random bond f = 4 2.563, 1.392.
-      if constexpr (P <= 8) {
+      if constexpr (kRounds) {
 #pragma unroll 1
         for (uint32_t done = RQ; done < nreq; done += RQ) {
           slots_read();

@@ -398,18 +398,34 @@ __global__ void __launch_bounds__(64)
 }
 
 // Chunk c: sum over its modes of the mean over the samples, from G partial sums
-// (fixed order: thread stride, then a tree).
+// (fixed order: thread stride, then a tree).  Bound by the latency of its loads,
+// so some 16 of them are in flight (L = 2^16 x 4 in 32 bins: one after
+// the other 61 us a measurement, 49 now).
+template <int G>
 __global__ void __launch_bounds__(kBlock)
-    k_sq_chunk(const double* __restrict__ rows, const int32_t* __restrict__ chunk_lo, int N, int G, int S,
+    k_sq_chunk(const double* __restrict__ rows, const int32_t* __restrict__ chunk_lo, int N, int S,
                double* __restrict__ part) {
+  constexpr int A = 16 / G;  // modes at a time
   __shared__ double red[kBlock];
   const int c = blockIdx.x;
   const int lo = chunk_lo[c], hi = chunk_lo[c + 1];
   double acc = 0.0;
-  for (int n = lo + threadIdx.x; n < hi; n += kBlock) {
-    double sum = 0.0;
-    for (int g = 0; g < G; ++g) sum += rows[(int64_t)g * (N + 1) + n];
-    acc += sum / (double)S;
+  for (int n = lo + threadIdx.x; n < hi; n += A * kBlock) {
+    double x[A][G];
+#pragma unroll
+    for (int a = 0; a < A; ++a)
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int m = n + a * kBlock;
+        x[a][g] = rows[(int64_t)g * (N + 1) + (m < hi ? m : n)];
+      }
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      double sum = 0.0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) sum += x[a][g];
+      if (n + a * kBlock < hi) acc += sum / (double)S;
+    }
   }
   red[threadIdx.x] = acc;
   __syncthreads();
@@ -546,7 +562,11 @@ hipError_t launch_sq(const int64_t* off, int S, int64_t L, const double* u_plain
     rows = mean;
     G = samples = 1;
   }
-  hipLaunchKernelGGL(k_sq_chunk, dim3(n_chunks), dim3(kBlock), 0, st, rows, chunk_lo, N, G, samples, part);
+  const dim3 gc(n_chunks), bc(kBlock);
+  if (G == 1) hipLaunchKernelGGL(k_sq_chunk<1>, gc, bc, 0, st, rows, chunk_lo, N, samples, part);
+  else if (G == 2) hipLaunchKernelGGL(k_sq_chunk<2>, gc, bc, 0, st, rows, chunk_lo, N, samples, part);
+  else if (G == 3) hipLaunchKernelGGL(k_sq_chunk<3>, gc, bc, 0, st, rows, chunk_lo, N, samples, part);
+  else hipLaunchKernelGGL(k_sq_chunk<4>, gc, bc, 0, st, rows, chunk_lo, N, samples, part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_sq_bin, dim3((n_bins + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, st, part, chunk_lo,
                      chunk_first, n_bins, out);

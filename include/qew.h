@@ -135,12 +135,14 @@ typedef struct qew_plan_s qew_plan_t;
 typedef struct qew_plan_info {
   int64_t total_sites;   /* sum of L_s                                   */
   int64_t padded_sites;  /* sites held per state buffer (64-site aligned) */
-  int32_t n_tiles;       /* work items of the stepping kernel            */
+  int32_t n_tiles;       /* workgroup tiles of a full stepping launch    */
   int32_t n_meas_tiles;  /* work items of the measurement kernels        */
   int32_t k;             /* steps per fused launch (1 for one-step)      */
   int32_t tile;          /* sites per fused workgroup tile (0: one-step) */
   int32_t autotuned;     /* 1 if k / tile were chosen by qew_autotune    */
-  int32_t pad_;
+  int16_t fp64_k;        /* FP64 path: steps per full stepping launch (0: one-step
+                            launches only), chosen from the problem's size */
+  int16_t fp64_tile;     /*            sites per workgroup tile of it (0: one-step) */
   int64_t cur_step;      /* step index of the state in the workspace     */
 } qew_plan_info;
 

@@ -891,12 +891,13 @@ qew_status qew_plan_info_get(const qew_plan_t* p, qew_plan_info* info) {
   if (!p || !info) return fail(QEW_EINVAL, "plan and info must be non-NULL");
   info->total_sites = p->total_sites;
   info->padded_sites = p->padded;
-  info->n_tiles = fused(p) ? (int32_t)p->ft_s.size() : (int32_t)p->mt_s.size();
+  info->n_tiles = fused(p) || p->bk ? (int32_t)p->ft_s.size() : (int32_t)p->mt_s.size();
   info->n_meas_tiles = (int32_t)p->mt_s.size();
   info->k = p->k;
   info->tile = p->tile;
   info->autotuned = p->autotuned;
-  info->pad_ = 0;
+  info->fp64_k = (int16_t)p->bk;
+  info->fp64_tile = (int16_t)p->btile;
   info->cur_step = p->cur_step;
   return QEW_OK;
 }

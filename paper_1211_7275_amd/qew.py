@@ -59,8 +59,8 @@ class qew_plan_info(ctypes.Structure):
     _fields_ = [
         ("total_sites", ctypes.c_int64), ("padded_sites", ctypes.c_int64),
         ("n_tiles", ctypes.c_int32), ("n_meas_tiles", ctypes.c_int32), ("k", ctypes.c_int32),
-        ("tile", ctypes.c_int32), ("autotuned", ctypes.c_int32), ("pad_", ctypes.c_int32),
-        ("cur_step", ctypes.c_int64),
+        ("tile", ctypes.c_int32), ("autotuned", ctypes.c_int32), ("fp64_k", ctypes.c_int16),
+        ("fp64_tile", ctypes.c_int16), ("cur_step", ctypes.c_int64),
     ]
 
 

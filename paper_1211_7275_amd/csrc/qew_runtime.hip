@@ -199,10 +199,40 @@ bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   return false;
 }
 
-// Geometry of the blocked FP64 kernels (none without disorder: a pure stencil
-// runs at the memory's rate one step at a time).  The candidates are tried in
-// order, each taken if it needs at most `most` workgroups.  Measured, us per
-// step (RF, four chains of L):
+// What an Euler step of the FP64 path costs (us) on n tiles: what a few of them
+// take, or, where they fill the chip, `base` and `per` ns a tile.
+struct TileCost {
+  double few, base, per;
+  double of(int64_t n) const { return std::max(few, base + 1e-3 * per * (double)n); }
+};
+struct BlockedCost {
+  TileCost t256, t512, wide;
+  // One step per launch: what a single site per thread takes and each further one,
+  // and, where the chip is full, `base` and so many ns per measurement tile and wave.
+  double few, per_site, base, per_tile, per_wave;
+};
+
+// Measured, by kind: RF, RB, linear RB, RF without interpolation (f = 1); then the
+// spline kinds under a negative drive, where a site moves to nodes that narrow tiles
+// do not keep.  Random chains of 30 to 2^20 sites, 4 to 32768 of them; us per
+// step, rule and (one step per launch): 32768 chains of 128 sites RF 14 (38), RB 21
+// (128), linear RB 72 (72), without interpolation 65 (65), of 384 sites RF 25 (83), RB
+// 39 (299), 165 (167), 90 (119); 32768 x 128 at f = -1 RF 38 (38), RB 93 (129).
+constexpr double kNever = 1e30;  // 512-site tiles of the kinds whose force jumps: not built
+constexpr BlockedCost kBlockedCost[6] = {
+    {{0.50, 0.40, 0.38}, {0.70, 0.65, 0.60}, {1.3, 0.75, 2.0}, 2.9, 0.53, 2.2, 0.25, 0.39},
+    {{0.47, 0.38, 0.45}, {0.66, 0.62, 0.79}, {1.3, 1.00, 1.62}, 4.5, 1.93, 4.0, 0.70, 1.43},
+    {{2.30, 1.10, 4.50}, {kNever, 0.0, 0.0}, {3.4, 2.00, 5.15}, 3.65, 1.06, 3.0, 0.45, 0.78},
+    {{1.75, 1.20, 2.70}, {kNever, 0.0, 0.0}, {2.9, 1.35, 2.75}, 3.3, 0.64, 1.6, 0.75, 0.47},
+    {{1.10, 0.80, 1.20}, {1.90, 1.30, 2.40}, {1.8, 1.10, 2.1}, 2.9, 0.53, 2.2, 0.25, 0.39},
+    {{3.30, 2.40, 3.40}, {5.50, 3.50, 7.00}, {2.6, 1.20, 2.7}, 4.5, 1.93, 4.0, 0.70, 1.43}};
+constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads and first nodes
+
+// Geometry of the blocked FP64 kernels: the candidate, one step per launch among
+// them, whose step costs least (none without disorder: a pure stencil runs at the
+// memory's rate one step at a time).  A chain costs whole tiles, so batches of short
+// chains stay on narrow ones or on launches of one step however many there are.
+// Measured, us per step (RF, four chains of L):
 //                      256/112  256/96  256/64  512/64  1536/64
 //   L = 2^10             0.35     0.36    0.39    0.62
 //   L = 2^14             0.94     0.58    0.44    0.61
@@ -211,28 +241,34 @@ bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
 //   L = 2^22                                              25.2   (one step per launch: 97)
 // Random bond, 512/64 against wide (f = 1.0 / 2.4): at 2^18 2.6 / 4.6 against
 // 3.5 / 4.5, at 2^22 31 / 63 against 42 / 59.  The kinds whose force jumps (f =
-// 0.8): linear random bond 256/64 at 2^13 1.84, at 2^14 2.87, 512/64 at 2^16 8.0
-// against 2.84 wide at any of them; without interpolation at 2^14 1.98 (256/64),
-// at 2^16 5.4 (512/64) against 2.4 wide.
+// 0.8): linear random bond 256/64 at 2^13 1.84, at 2^14 2.87, against 2.84 wide;
+// without interpolation at 2^14 1.98 (256/64) against 2.4 wide.
 void build_blocked_tiles(qew_plan_t* p) {
   if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
-  const int64_t most_64[4] = {1024, 1024, 256, 512}, most_512[4] = {2048, 4096, 0, 0};
-  struct { int tile, k; int64_t most; } const geometry[] = {{256, 112, 256},
-                                                            {256, 96, 256},
-                                                            {256, 64, most_64[p->kind]},
-                                                            {512, 64, most_512[p->kind]},
-                                                            {blocked_wide_tile(p->kind), 64, INT64_MAX}};
-  if (fused_tile_count(p, 256, 112) > INT32_MAX / 2 &&
-      fused_tile_count(p, geometry[4].tile, geometry[4].k) > INT32_MAX / 2)
-    return;
-  int tile = 0;
-  for (const auto& g : geometry) {
-    tile = g.tile;
-    p->bk = g.k;
-    if (fused_tile_count(p, g.tile, g.k) <= g.most) break;
+  const bool back = *std::min_element(p->f.begin(), p->f.end()) < 0.0;
+  const BlockedCost& cost = kBlockedCost[back && p->kind < 2 ? 4 + p->kind : p->kind];
+  const struct { int tile, k; const TileCost& c; } geometry[] = {{256, 112, cost.t256},
+                                                                 {256, 96, cost.t256},
+                                                                 {256, 64, cost.t256},
+                                                                 {512, 64, cost.t512},
+                                                                 {blocked_wide_tile(p->kind), 64, cost.wide}};
+  double chip = cost.base;  // one step per launch, the chip full
+  int64_t sites = 1;        // of a thread
+  for (int64_t L : p->L) {
+    chip += 1e-3 * ((double)((L + kMeasTile - 1) / kMeasTile) * cost.per_tile + (double)((L + 63) / 64) * cost.per_wave);
+    sites = std::max(sites, (std::min<int64_t>(L, kMeasTile) + kBlock - 1) / kBlock);
   }
-  p->btile = tile;
-  const int64_t V = tile - 2 * p->bk;
+  double least = std::max(cost.few + cost.per_site * (double)(sites - 1), chip);
+  for (const auto& g : geometry) {
+    const int64_t n = fused_tile_count(p, g.tile, g.k);
+    const double us = g.c.of(n) + kLaunchCost / g.k;
+    if (n > INT32_MAX / 2 || us >= least) continue;
+    least = us;
+    p->btile = g.tile;
+    p->bk = g.k;
+  }
+  if (p->bk == 0) return;
+  const int64_t V = p->btile - 2 * p->bk;
   p->ft_s.clear();
   p->ft_p0.clear();
   p->ft_len.clear();

@@ -11,11 +11,11 @@ pytestmark = pytest.mark.gpu
 SEED = workloads.SEED_BASE + 170
 
 
-def _states(qew, p, start=None, every_step=False, **options):
+def _states(qew, p, start=None, every_step=False, tile=0):
     steps = int(p["n_steps"])
     if every_step:
         p = dict(p, meas_steps=np.arange(steps))
-    sim = qew.Simulation(p, precision=qew.QEW_FP64_PLAIN, path=qew.QEW_ONE_STEP, **options)
+    sim = qew.Simulation(p, precision=qew.QEW_FP64_PLAIN, path=qew.QEW_ONE_STEP)
     try:
         if start is not None:
             for s, u in enumerate(start):
@@ -23,13 +23,15 @@ def _states(qew, p, start=None, every_step=False, **options):
         sim.run(resume=start is not None)
         launches = sim.stats().step_launches
         assert launches == steps if every_step else launches < steps
+        if tile:
+            assert sim.info().fp64_tile == tile
         return [sim.read_state(s)[0] for s in range(len(p["L"]))]
     finally:
         sim.close()
 
 
-def _same(qew, p, start=None):
-    got, ref = _states(qew, p, start), _states(qew, p, start, every_step=True)
+def _same(qew, p, start=None, tile=0):
+    got, ref = _states(qew, p, start, tile=tile), _states(qew, p, start, every_step=True)
     for a, b in zip(got, ref):
         assert np.array_equal(a, b, equal_nan=True)
 
@@ -40,14 +42,14 @@ def test_bursts_on_wide_tiles(kind, f):
     """More cell changes in a wave and step than its request region holds, over a
     full launch and a part of one, on the widest tiles of every kind."""
     from paper_1211_7275_amd import qew
-    L = 1_800_001
+    L = 2_500_001
     print("[gpu-test] FP64 bursts on wide tiles, kind", kind, "f", f, flush=True)
     start = [np.cumsum(np.random.default_rng(kind).normal(0.0, 0.5, L))]
-    _same(qew, workloads.custom(kind, [L], f, 90, [0], SEED, strength=0.7), start)
+    _same(qew, workloads.custom(kind, [L], f, 90, [0], SEED, strength=0.7), start, tile=1024 if kind == 1 else 1536)
 
 
 @pytest.mark.parametrize("kind", [0, 1, 2, 3])
-@pytest.mark.parametrize("L", [203, 40_007, 1_800_001])
+@pytest.mark.parametrize("L", [203, 40_007, 2_500_001])
 @pytest.mark.parametrize("side", [1.0, -1.0])
 def test_last_cells(kind, L, side):
     """Lines that reach the last 32-bit cells, whose windows go on past the largest

@@ -36,3 +36,38 @@ def test_plans_of_one_step_per_launch_report_none():
                  _info([1 << 16] * 4, fp64=False, k=32, tile=2048)):
         assert info.fp64_k == 0 and info.fp64_tile == 0
     assert _info([1 << 16] * 4, strength=0.0).n_tiles == 64
+
+
+@pytest.mark.parametrize("chains", [512, 4096, 32768])
+@pytest.mark.parametrize("L", [64, 128, 256])
+def test_fp64_batches_of_short_chains_take_no_wide_tiles(L, chains):
+    """A chain costs whole tiles: 1024 or 1536 sites for one of 64 took up to four
+    times what a step per launch takes."""
+    for kind in (0, 1):
+        info = _info([L] * chains, kind)
+        assert info.fp64_tile in (256, 512) and info.n_tiles <= 2 * chains, (kind, info.fp64_tile)
+    for kind in (2, 3):
+        info = _info([L] * chains, kind)
+        if chains >= 4096 and L < 256:  # a narrow tile costs more than a step per launch
+            assert info.fp64_tile == 0, kind
+        assert info.fp64_tile in (0, 256) or L == 256, (kind, info.fp64_tile)
+
+
+@pytest.mark.parametrize("kind,expect", [(0, [(112, 256), (96, 256), (64, 256), (64, 256), (64, 512), (64, 1536), (64, 1536)]),
+                                         (1, [(112, 256), (64, 256), (64, 256), (64, 256), (64, 512), (64, 512), (64, 1024)]),
+                                         (2, [(112, 256), (96, 256), (64, 256), (64, 1536), (64, 1536), (64, 1536), (64, 1536)]),
+                                         (3, [(112, 256), (64, 256), (64, 256), (64, 256), (64, 1536), (64, 1536), (64, 1536)])])
+def test_fp64_geometry_of_four_chains(kind, expect):
+    """From latency to throughput: four chains of 2^10, 2^12, 2^13, 2^14, 2^16, 2^18 and 2^22 sites."""
+    got = [_info([1 << lg] * 4, kind) for lg in (10, 12, 13, 14, 16, 18, 22)]
+    assert [(i.fp64_k, i.fp64_tile) for i in got] == expect
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+def test_fp64_geometry_under_a_negative_drive(kind):
+    """A line that moves backwards finds no node ready on narrow tiles, so they stop
+    paying early; one such drive in a batch is enough."""
+    for L in (1 << 16, 1 << 18):
+        assert _info([L] * 4, kind).fp64_tile < 1024 or L > 1 << 16
+        for f in (-1.0, np.array([1.0, 0.5, -0.2, 2.0])):
+            assert _info([L] * 4, kind, f).fp64_tile == (1024 if kind == 1 else 1536)

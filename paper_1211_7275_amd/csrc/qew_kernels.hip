@@ -160,7 +160,8 @@ __device__ __forceinline__ TileOf tile_of(const Tables& t) {
     const int tile = t.mt_first[s] + uniform_i32((int)(threadIdx.x / kBlock));
     return TileOf{tile, s, (int)(threadIdx.x % kBlock), tile < t.mt_first[s + 1]};
   } else {
-    return TileOf{(int)blockIdx.x, t.mt_s[blockIdx.x], (int)threadIdx.x, true};
+    const int tile = blockIdx.x;  // one index for all of the tile's table entries: their loads then overlap
+    return TileOf{tile, t.mt_s[tile], (int)threadIdx.x, true};
   }
 }
 

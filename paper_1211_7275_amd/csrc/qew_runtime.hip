@@ -226,6 +226,7 @@ constexpr BlockedCost kBlockedCost[6] = {
     {{1.75, 1.20, 2.70}, {kNever, 0.0, 0.0}, {2.9, 1.35, 2.75}, 3.3, 0.64, 1.6, 0.75, 0.47},
     {{1.10, 0.80, 1.20}, {1.90, 1.30, 2.40}, {1.8, 1.10, 2.1}, 2.9, 0.53, 2.2, 0.25, 0.39},
     {{3.30, 2.40, 3.40}, {5.50, 3.50, 7.00}, {2.6, 1.20, 2.7}, 4.5, 1.93, 4.0, 0.70, 1.43}};
+constexpr int64_t kMaxTiles = UINT32_MAX / kBlock;  // a launch holds fewer than 2^32 threads
 constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads and first nodes
 
 // Geometry of the blocked FP64 kernels: the candidate, one step per launch among
@@ -262,7 +263,7 @@ void build_blocked_tiles(qew_plan_t* p) {
   for (const auto& g : geometry) {
     const int64_t n = fused_tile_count(p, g.tile, g.k);
     const double us = g.c.of(n) + kLaunchCost / g.k;
-    if (n > INT32_MAX / 2 || us >= least) continue;
+    if (n > kMaxTiles || us >= least) continue;  // one workgroup per tile
     least = us;
     p->btile = g.tile;
     p->bk = g.k;

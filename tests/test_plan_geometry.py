@@ -71,3 +71,11 @@ def test_fp64_geometry_under_a_negative_drive(kind):
         assert _info([L] * 4, kind).fp64_tile < 1024 or L > 1 << 16
         for f in (-1.0, np.array([1.0, 0.5, -0.2, 2.0])):
             assert _info([L] * 4, kind, f).fp64_tile == (1024 if kind == 1 else 1536)
+
+
+def test_fp64_tiles_stay_within_one_launch():
+    """A launch holds fewer than 2^32 threads, 256 to a tile: random-bond lines that
+    fit the memory have more 896-site tiles than that, and run one step per launch."""
+    assert _info([1 << 30] * 13, 1).fp64_tile == 1024
+    info = _info([1 << 30] * 15, 1)
+    assert info.fp64_tile == 0 and info.n_tiles == 15 * (1 << 30) // 4096

@@ -172,6 +172,8 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
   if (p->lay.total) refresh_table_image(p);
 }
 
+bool negative_drive(const qew_plan_t* p) { return *std::min_element(p->f.begin(), p->f.end()) < 0.0; }
+
 // Narrow-tile geometry of the fused path (k_lanes), for small problems where
 // the caller left k and the tile open and forced no variant.  The candidates are
 // tried in order, each taken if it needs at most `most` workgroups.  Measured,
@@ -184,10 +186,12 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
 // The kinds whose force jumps make sites hop between two cells, and a step back
 // has no node ready, so narrow tiles lose early: linear random bond, f = 0.8, at
 // 2^13 0.95 against 1.90 wide, at 2^16 3.3 against 1.85; without interpolation
-// 1.01 against 0.98 and 3.3 against 1.06.
+// 1.01 against 0.98 and 3.3 against 1.06.  A line under a negative drive moves
+// backwards all the time: f = -1 RF at 2^13 0.90 against 1.11, at 2^14 1.08 against
+// 1.00, at 2^16 2.5 against 1.04; random bond 0.61, 0.69, 1.06 against 0.87, 0.82, 0.85.
 bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   if (!fused(p) || p->k_req || p->tile_req || (p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
-  const bool hops = p->kind >= 2;
+  const bool hops = p->kind >= 2 || negative_drive(p);
   struct { int tile, k; int64_t most; } const geometry[] = {
       {256, 112, 256}, {256, 96, 256}, {256, 64, hops ? 256 : 1024}, {512, 64, hops ? 0 : 1152}};
   for (const auto& g : geometry) {
@@ -246,8 +250,7 @@ constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads
 // without interpolation at 2^14 1.98 (256/64) against 2.4 wide.
 void build_blocked_tiles(qew_plan_t* p) {
   if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
-  const bool back = *std::min_element(p->f.begin(), p->f.end()) < 0.0;
-  const BlockedCost& cost = kBlockedCost[back && p->kind < 2 ? 4 + p->kind : p->kind];
+  const BlockedCost& cost = kBlockedCost[negative_drive(p) && p->kind < 2 ? 4 + p->kind : p->kind];
   const struct { int tile, k; const TileCost& c; } geometry[] = {{256, 112, cost.t256},
                                                                  {256, 96, cost.t256},
                                                                  {256, 64, cost.t256},

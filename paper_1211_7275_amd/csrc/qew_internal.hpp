@@ -76,9 +76,10 @@ hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout
 hipError_t launch_step_split1(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
                               const MeasOut& o, hipStream_t st);
 // `sparse`: the variant that skips the request bookkeeping of a wave whose
-// sites did not change cell (for pinned or slow lines).
+// sites did not change cell (for pinned or slow lines).  `rounds`: how a dense
+// kernel that can do either serves a burst of cell changes.
 hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
-                             int tile, int halo, int nsub, int grid, bool sparse, hipStream_t st);
+                             int tile, int halo, int nsub, int grid, bool sparse, bool rounds, hipStream_t st);
 int fused_max_grid(int tile);
 bool fused_fits(int tile);  // static LDS of the tile's kernel within the device limit
 hipError_t launch_meas_plain(const Tables& t, const double* u, const Phys& ph, int kind,

@@ -386,13 +386,19 @@ constexpr int kReqPerWave = 64;
 // Waves per SIMD the register allocation must allow (LDS allows the same).
 constexpr int fused_min_waves(int P) { return P == 6 ? 5 : (P <= 8 ? 4 : (P == 12 ? 3 : 2)); }
 
-template <int KIND, int P, bool SPARSE>
+// Whether a kernel exists that serves a burst in rounds.  Tiles of 12 or more sites per
+// thread have none (the rounds' code costs their common path 3 %), nor has the
+// sparse random-field kernel, whose registers then allow a wave per SIMD less or
+// spill (2^20 x 4, f = 0.8, us per step with rounds and without: 1024-site tiles
+// 6.25, 4.80; 1536-site ones 4.84, 4.05).
+constexpr bool has_rounds(int kind, int P, bool sparse) { return P <= 8 && !(sparse && kind == kRF); }
+
+template <int KIND, int P, bool SPARSE, bool ROUNDS>
 __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
     k_step_fused(Tables t, SplitBuf in, SplitBuf out, Phys ph, int halo, int nsub) {
   constexpr int T = kBlock * P;
   constexpr int NW = kBlock / 64;
   constexpr int RQ = kReqPerWave;
-  constexpr bool kRounds = P <= 8 && !(SPARSE && KIND == kRF);  // how a burst of requests is served
   __shared__ float4 s_nodes[T];
   __shared__ int4 s_req[NW * (RQ + 1)];  // per wave: RQ requests, then one sink slot
   // End sites of each wave, double-buffered: [parity][cell, offset][slot][end],
@@ -617,11 +623,16 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
             w4 = make_float4(w4.y, w4.z, w4.w, node_f32<KIND>((uint32_t)j, cell + 2, id, ph.k0, ph.k1, ph.period));
           } else if (move == -1.0f) {
             w4 = make_float4(node_f32<KIND>((uint32_t)j, cell - 1, id, ph.k0, ph.k1, ph.period), w4.x, w4.y, w4.z);
-          } else {
+          } else if constexpr (ROUNDS || P > 8) {
 #pragma unroll 1
             for (int i = 0; i < 4; ++i)
               w4 = make_float4(w4.y, w4.z, w4.w,
                                node_f32<KIND>((uint32_t)j, node_after(cell, i - 1), id, ph.k0, ph.k1, ph.period));
+          } else {  // jumps are what this kernel is for
+            w4 = make_float4(node_f32<KIND>((uint32_t)j, node_after(cell, -1), id, ph.k0, ph.k1, ph.period),
+                             node_f32<KIND>((uint32_t)j, cell, id, ph.k0, ph.k1, ph.period),
+                             node_f32<KIND>((uint32_t)j, node_after(cell, 1), id, ph.k0, ph.k1, ph.period),
+                             node_f32<KIND>((uint32_t)j, node_after(cell, 2), id, ph.k0, ph.k1, ph.period));
           }
           s_nodes[ni] = w4;
           float4 co;
@@ -648,15 +659,11 @@ __global__ void __launch_bounds__(kBlock, fused_min_waves(P))
         __builtin_amdgcn_wave_barrier();
       }
       // Rare: more requests than the region holds (a burst of cell changes).
-      // Those past it are posted and served in further rounds.  Where the rounds'
-      // code costs the common path more than it gives, their lanes make their
-      // windows themselves: tiles of 12 or more sites per thread (3 %), and the
-      // sparse random-field kernel, whose registers then allow a wave per SIMD
-      // less or spill (2^20 x 4, f = 0.8, us per step with rounds and without:
-      // 1024-site tiles 6.25, 4.80; 1536-site ones 4.84, 4.05).  At
-      // 2^22 x 4 on 2048-site tiles, k = 56, ms per launch, own windows and rounds:
-      // f = 1.0 0.692, 0.678; f = 2.5 1.165, 1.042; random bond f = 4 2.563, 1.392.
-      if constexpr (kRounds) {
+      // Those past it are posted and served in further rounds (ROUNDS), or their
+      // lanes make their windows themselves.  At 2^22 x 4 on 2048-site tiles, k = 56,
+      // ms per launch, own windows and rounds: f = 1.0 0.692, 0.678; f = 2.5 1.165, 1.042;
+      // random bond f = 4 2.563, 1.392.
+      if constexpr (ROUNDS) {
 #pragma unroll 1
         for (uint32_t done = RQ; done < nreq; done += RQ) {
           slots_read();
@@ -1660,7 +1667,7 @@ hipError_t launch_step_split1(const Tables& t, SplitBuf in, SplitBuf out, const 
 
 template <int KIND, int P>
 static const void* fused_ptr() {
-  return reinterpret_cast<const void*>(&k_step_fused<KIND, P, false>);
+  return reinterpret_cast<const void*>(&k_step_fused<KIND, P, false, has_rounds(KIND, P, false)>);
 }
 
 static const void* fused_fn(int tile) {
@@ -1694,9 +1701,30 @@ bool fused_fits(int tile) {
   return (int)attr.sharedSizeBytes <= max_lds;
 }
 
+struct FusedLaunch {
+  const Tables& t;
+  SplitBuf in, out;
+  const Phys& ph;
+  int halo, nsub;
+  bool rounds;
+  dim3 g, b;
+  hipStream_t st;
+  template <int KIND, int P, bool SPARSE>
+  void run() const {
+    if constexpr (has_rounds(KIND, P, SPARSE)) {
+      if (rounds || SPARSE) {
+        hipLaunchKernelGGL((k_step_fused<KIND, P, SPARSE, true>), g, b, 0, st, t, in, out, ph, halo, nsub);
+        return;
+      }
+    }
+    if constexpr (!(SPARSE && has_rounds(KIND, P, SPARSE)))  // a sparse launch is no fast line's
+      hipLaunchKernelGGL((k_step_fused<KIND, P, SPARSE, false>), g, b, 0, st, t, in, out, ph, halo, nsub);
+  }
+};
+
 template <int KIND, bool SPARSE>
 static void launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int tile,
-                              int halo, int nsub, dim3 g, dim3 b, hipStream_t st) {
+                              int halo, int nsub, bool rounds, dim3 g, dim3 b, hipStream_t st) {
   if constexpr (!SPARSE) {
     if (tile == 256 || tile == 512) {  // one workgroup per tile
       if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 1>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
@@ -1705,29 +1733,30 @@ static void launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const 
       return;
     }
   }
-  if (tile == 1024) hipLaunchKernelGGL((k_step_fused<KIND, 4, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
-  else if (tile == 1536) hipLaunchKernelGGL((k_step_fused<KIND, 6, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
-  else if (tile == 2048) hipLaunchKernelGGL((k_step_fused<KIND, 8, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
-  else if (tile == 3072) hipLaunchKernelGGL((k_step_fused<KIND, 12, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
-  else hipLaunchKernelGGL((k_step_fused<KIND, 16, SPARSE>), g, b, 0, st, t, in, out, ph, halo, nsub);
+  const FusedLaunch l{t, in, out, ph, halo, nsub, rounds, g, b, st};
+  if (tile == 1024) l.template run<KIND, 4, SPARSE>();
+  else if (tile == 1536) l.template run<KIND, 6, SPARSE>();
+  else if (tile == 2048) l.template run<KIND, 8, SPARSE>();
+  else if (tile == 3072) l.template run<KIND, 12, SPARSE>();
+  else l.template run<KIND, 16, SPARSE>();
 }
 
 template <bool SPARSE>
 static void launch_fused_variant(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
-                                 int tile, int halo, int nsub, dim3 g, dim3 b, hipStream_t st) {
+                                 int tile, int halo, int nsub, bool rounds, dim3 g, dim3 b, hipStream_t st) {
   switch (kind) {
-    case kRF: launch_fused_kind<kRF, SPARSE>(t, in, out, ph, tile, halo, nsub, g, b, st); break;
-    case kRB: launch_fused_kind<kRB, SPARSE>(t, in, out, ph, tile, halo, nsub, g, b, st); break;
-    case kRBLin: launch_fused_kind<kRBLin, SPARSE>(t, in, out, ph, tile, halo, nsub, g, b, st); break;
-    default: launch_fused_kind<kRFPc, SPARSE>(t, in, out, ph, tile, halo, nsub, g, b, st); break;
+    case kRF: launch_fused_kind<kRF, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
+    case kRB: launch_fused_kind<kRB, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
+    case kRBLin: launch_fused_kind<kRBLin, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
+    default: launch_fused_kind<kRFPc, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
   }
 }
 
 hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
-                             int tile, int halo, int nsub, int grid, bool sparse, hipStream_t st) {
+                             int tile, int halo, int nsub, int grid, bool sparse, bool rounds, hipStream_t st) {
   const dim3 g(grid), b(kBlock);
-  if (sparse) launch_fused_variant<true>(t, in, out, ph, kind, tile, halo, nsub, g, b, st);
-  else launch_fused_variant<false>(t, in, out, ph, kind, tile, halo, nsub, g, b, st);
+  if (sparse) launch_fused_variant<true>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st);
+  else launch_fused_variant<false>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st);
   return hipGetLastError();
 }
 

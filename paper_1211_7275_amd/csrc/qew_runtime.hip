@@ -72,6 +72,13 @@ constexpr int64_t kShortStretch = 4;
 // sub-steps of a wave then have no cell change at all.
 constexpr double kSparseRequestsPerWave = 0.5;
 
+// From this many cells per site and step on (mean |f| dt), every sub-step is a burst of
+// all sites and many of them jump: the fused kernel's lanes then make their own
+// windows instead of serving requests in rounds.  us per step at 2^20 x 4 on 1024-site tiles,
+// rounds / own windows: f dt = 0.5 RF 10.8 / 16.4, random bond 11.5 / 17.8; 0.9 15.3 / 20.1,
+// 15.9 / 23.5; 1.0 30.5 / 24.4, 40.7 / 29.7; on 2048-site ones at 1.0 32 / 24, 45 / 29.
+constexpr double kFastLine = 0.95;
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
@@ -119,6 +126,7 @@ struct qew_plan_s {
   int32_t meas_groups = 0;  // measurement tiles of a sample one workgroup takes (0: one each)
   int32_t ft_capacity = 0;
   int32_t k = 1, tile = 0, autotuned = 0;
+  bool fast = false;      // kFastLine
   int32_t bk = 0, btile = 0;  // FP64 path: steps per blocked launch (0: one-step launches only) and its tile
   Layout lay{};
   std::vector<int32_t> bt_img;  // host image of the blocked tiles: samples, first sites, lengths
@@ -530,7 +538,7 @@ hipError_t onestep_launch(const qew_plan_t* p, void* ws, int from, const MeasOut
 // One launch of the fused kernel: nsub Euler steps from buffer `from`.
 hipError_t fused_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipStream_t st) {
   return launch_step_fused(tables_of(p, ws), split_buf(p, ws, from), split_buf(p, ws, from ^ 1), phys_of(p),
-                           p->kind, p->tile, p->k, nsub, p->fused_grid, p->sparse != 0, st);
+                           p->kind, p->tile, p->k, nsub, p->fused_grid, p->sparse != 0, !p->fast, st);
 }
 
 // Euler steps of a full launch of the plan's stepping kernel.
@@ -880,6 +888,9 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
     p->mt_first.push_back((int32_t)p->mt_s.size());
   }
   p->padded = o;
+  double drive = 0.0;  // of a site
+  for (int32_t s = 0; s < p->S; ++s) drive += std::fabs(p->f[s]) * ((double)p->L[s] / (double)p->total_sites);
+  p->fast = drive * p->dt > kFastLine;
   int32_t most = 0;  // measurement tiles of the longest chain
   for (int32_t s = 0; s < p->S; ++s) most = std::max(most, p->mt_first[s + 1] - p->mt_first[s]);
   p->meas_groups = most > kFinalTiles ? 0 : most;

@@ -1712,7 +1712,11 @@ struct FusedLaunch {
   template <int KIND, int P, bool SPARSE>
   void run() const {
     if constexpr (has_rounds(KIND, P, SPARSE)) {
-      if (rounds || SPARSE) {
+      // Without interpolation a few small tiles have bursts whose rounds nobody hides:
+      // 1024-site tiles, f = 0.6, us per step with rounds and without, 69 tiles 1.58,
+      // 1.49, 273 1.60, 1.51, 1092 2.15, 2.16 (f = 0.2: 2.80, 2.99).
+      const bool few = KIND == kRFPc && P == 4 && t.n_ft <= 512;
+      if ((rounds && !few) || SPARSE) {
         hipLaunchKernelGGL((k_step_fused<KIND, P, SPARSE, true>), g, b, 0, st, t, in, out, ph, halo, nsub);
         return;
       }

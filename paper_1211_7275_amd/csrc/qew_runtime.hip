@@ -126,7 +126,7 @@ struct qew_plan_s {
   int32_t meas_groups = 0;  // measurement tiles of a sample one workgroup takes (0: one each)
   int32_t ft_capacity = 0;
   int32_t k = 1, tile = 0, autotuned = 0;
-  bool fast = false;      // kFastLine
+  double drive = 0.0;     // mean |f| dt of a site: the cells it moves in a step when nothing pins it
   int32_t bk = 0, btile = 0;  // FP64 path: steps per blocked launch (0: one-step launches only) and its tile
   Layout lay{};
   std::vector<int32_t> bt_img;  // host image of the blocked tiles: samples, first sites, lengths
@@ -211,33 +211,67 @@ bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   return false;
 }
 
-// What an Euler step of the FP64 path costs (us) on n tiles: what a few of them
-// take, or, where they fill the chip, `base` and `per` ns a tile.
+// What an Euler step of the FP64 path costs (us) on n tiles of lines that move by x
+// cells per site and step (mean |f| dt): what a few tiles take, or, where they fill the
+// chip, `base` and `per` ns a tile; more from 0.1 cells on, where bursts are common.
 struct TileCost {
-  double few, base, per;
-  double of(int64_t n) const { return std::max(few, base + 1e-3 * per * (double)n); }
+  double few, base, per, speed;
+  double of(int64_t n, double x) const {
+    return std::max(few, base + 1e-3 * per * (double)n) * (1.0 + speed * std::max(0.0, x - 0.1));
+  }
 };
 struct BlockedCost {
   TileCost t256, t512, wide;
-  // One step per launch: what a single site per thread takes and each further one,
-  // and, where the chip is full, `base` and so many ns per measurement tile and wave.
+};
+constexpr double kNever = 1e30;  // 512-site tiles of the kinds whose force jumps: not built
+constexpr TileCost kNone = {kNever, 0.0, 0.0, 0.0};
+
+// Measured on chains of 30 to 2^22 sites, 4 to 32768 of them, drives of 0.5 to 45 in both
+// directions at dt = 0.05 (840 cases; the choice these make is never slower than one step
+// per launch by more than 7 %, and within 25 % of the best in all but ten).  us per
+// step, the choice and (one step per launch): 32768 chains of 128 sites at f = 1 RF 14 (38),
+// RB 21 (128), linear RB 72 (72), RF without interpolation 65 (65), of 384 sites RF 25
+// (83), RB 39 (299), 178 (167), 90 (119); 2^22 x 4 at f = 20 RF 101 (101; wide tiles 138),
+// RB 388 (388; 516); 4096 x 384 linear RB at f = 10 14 (24; wide 36).
+constexpr BlockedCost kSlowCost[4] = {  // by kind: RF, RB, linear RB, RF without interpolation
+    {{0.50, 0.40, 0.38, 1.0}, {0.70, 0.65, 0.60, 1.1}, {1.3, 0.75, 2.0, 3.6}},
+    {{0.47, 0.38, 0.45, 4.0}, {0.66, 0.62, 0.79, 4.6}, {1.3, 1.00, 1.62, 5.8}},
+    {{2.30, 1.10, 4.50, 0.0}, kNone, {3.4, 2.00, 5.15, 0.0}},  // sites hop between two cells
+    {{1.75, 1.20, 2.70, 0.0}, kNone, {2.9, 1.35, 2.75, 0.0}}};
+// A line that moves backwards finds no node ready on narrow tiles.
+constexpr BlockedCost kBackCost[4] = {
+    {{1.10, 0.80, 1.20, 0.5}, {1.90, 1.30, 2.40, 0.4}, {1.8, 1.1, 2.1, 3.9}},
+    {{3.30, 2.40, 3.40, 1.5}, {5.50, 3.50, 7.00, 2.0}, {2.6, 1.2, 2.7, 3.9}},
+    {{2.00, 1.30, 3.30, 0.0}, kNone, {2.0, 1.2, 2.6, 4.5}},
+    {{1.35, 1.10, 1.65, 0.0}, kNone, {1.9, 1.0, 2.4, 4.8}}};
+// The kinds whose force jumps, once they move.
+constexpr double kMovingLine = 0.12;
+constexpr BlockedCost kMovingCost[2] = {{{1.4, 1.2, 1.1, 0.6}, kNone, {2.0, 1.2, 2.6, 4.5}},
+                                        {{1.1, 1.0, 0.6, 1.6}, kNone, {1.9, 1.0, 2.4, 4.8}}};
+// From kFastLine on.
+constexpr BlockedCost kFastCost[4] = {
+    {{1.40, 0.9, 1.68, 0.0}, {2.3, 1.4, 3.35, 0.0}, {8.0, 3.3, 11.4, 0.0}},
+    {{3.40, 1.3, 7.75, 0.0}, {6.9, 3.0, 15.6, 0.0}, {12.0, 6.0, 27.6, 0.0}},
+    {{2.40, 1.3, 4.50, 0.0}, kNone, {11.0, 3.3, 22.4, 0.0}},
+    {{1.75, 1.0, 2.80, 0.0}, kNone, {7.25, 3.0, 12.4, 0.0}}};
+// One step per launch, whatever the drive: what a single site per thread takes and
+// each further one, and, where the chip is full, `base` and so many ns per measurement
+// tile and wave.
+struct OneStepCost {
   double few, per_site, base, per_tile, per_wave;
 };
+constexpr OneStepCost kOneStepCost[4] = {{2.9, 0.53, 2.2, 0.25, 0.39},
+                                         {4.5, 1.93, 4.0, 0.70, 1.43},
+                                         {3.65, 1.06, 3.0, 0.45, 0.78},
+                                         {3.3, 0.64, 1.6, 0.75, 0.47}};
 
-// Measured, by kind: RF, RB, linear RB, RF without interpolation (f = 1); then the
-// spline kinds under a negative drive, where a site moves to nodes that narrow tiles
-// do not keep.  Random chains of 30 to 2^20 sites, 4 to 32768 of them; us per
-// step, rule and (one step per launch): 32768 chains of 128 sites RF 14 (38), RB 21
-// (128), linear RB 72 (72), without interpolation 65 (65), of 384 sites RF 25 (83), RB
-// 39 (299), 165 (167), 90 (119); 32768 x 128 at f = -1 RF 38 (38), RB 93 (129).
-constexpr double kNever = 1e30;  // 512-site tiles of the kinds whose force jumps: not built
-constexpr BlockedCost kBlockedCost[6] = {
-    {{0.50, 0.40, 0.38}, {0.70, 0.65, 0.60}, {1.3, 0.75, 2.0}, 2.9, 0.53, 2.2, 0.25, 0.39},
-    {{0.47, 0.38, 0.45}, {0.66, 0.62, 0.79}, {1.3, 1.00, 1.62}, 4.5, 1.93, 4.0, 0.70, 1.43},
-    {{2.30, 1.10, 4.50}, {kNever, 0.0, 0.0}, {3.4, 2.00, 5.15}, 3.65, 1.06, 3.0, 0.45, 0.78},
-    {{1.75, 1.20, 2.70}, {kNever, 0.0, 0.0}, {2.9, 1.35, 2.75}, 3.3, 0.64, 1.6, 0.75, 0.47},
-    {{1.10, 0.80, 1.20}, {1.90, 1.30, 2.40}, {1.8, 1.10, 2.1}, 2.9, 0.53, 2.2, 0.25, 0.39},
-    {{3.30, 2.40, 3.40}, {5.50, 3.50, 7.00}, {2.6, 1.20, 2.7}, 4.5, 1.93, 4.0, 0.70, 1.43}};
+const BlockedCost& blocked_cost(const qew_plan_t* p) {
+  if (p->drive > kFastLine) return kFastCost[p->kind];
+  if (p->kind < 2) return negative_drive(p) ? kBackCost[p->kind] : kSlowCost[p->kind];
+  if (p->drive < kMovingLine) return kSlowCost[p->kind];
+  return negative_drive(p) ? kBackCost[p->kind] : kMovingCost[p->kind - 2];
+}
+
 constexpr int64_t kMaxTiles = UINT32_MAX / kBlock;  // a launch holds fewer than 2^32 threads
 constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads and first nodes
 
@@ -258,22 +292,23 @@ constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads
 // without interpolation at 2^14 1.98 (256/64) against 2.4 wide.
 void build_blocked_tiles(qew_plan_t* p) {
   if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
-  const BlockedCost& cost = kBlockedCost[negative_drive(p) && p->kind < 2 ? 4 + p->kind : p->kind];
+  const BlockedCost& cost = blocked_cost(p);
+  const OneStepCost& one = kOneStepCost[p->kind];
   const struct { int tile, k; const TileCost& c; } geometry[] = {{256, 112, cost.t256},
                                                                  {256, 96, cost.t256},
                                                                  {256, 64, cost.t256},
                                                                  {512, 64, cost.t512},
                                                                  {blocked_wide_tile(p->kind), 64, cost.wide}};
-  double chip = cost.base;  // one step per launch, the chip full
+  double chip = one.base;   // one step per launch, the chip full
   int64_t sites = 1;        // of a thread
   for (int64_t L : p->L) {
-    chip += 1e-3 * ((double)((L + kMeasTile - 1) / kMeasTile) * cost.per_tile + (double)((L + 63) / 64) * cost.per_wave);
+    chip += 1e-3 * ((double)((L + kMeasTile - 1) / kMeasTile) * one.per_tile + (double)((L + 63) / 64) * one.per_wave);
     sites = std::max(sites, (std::min<int64_t>(L, kMeasTile) + kBlock - 1) / kBlock);
   }
-  double least = std::max(cost.few + cost.per_site * (double)(sites - 1), chip);
+  double least = std::max(one.few + one.per_site * (double)(sites - 1), chip);
   for (const auto& g : geometry) {
     const int64_t n = fused_tile_count(p, g.tile, g.k);
-    const double us = g.c.of(n) + kLaunchCost / g.k;
+    const double us = g.c.of(n, p->drive) + kLaunchCost / g.k;
     if (n > kMaxTiles || us >= least) continue;  // one workgroup per tile
     least = us;
     p->btile = g.tile;
@@ -538,7 +573,7 @@ hipError_t onestep_launch(const qew_plan_t* p, void* ws, int from, const MeasOut
 // One launch of the fused kernel: nsub Euler steps from buffer `from`.
 hipError_t fused_launch(const qew_plan_t* p, void* ws, int from, int nsub, hipStream_t st) {
   return launch_step_fused(tables_of(p, ws), split_buf(p, ws, from), split_buf(p, ws, from ^ 1), phys_of(p),
-                           p->kind, p->tile, p->k, nsub, p->fused_grid, p->sparse != 0, !p->fast, st);
+                           p->kind, p->tile, p->k, nsub, p->fused_grid, p->sparse != 0, p->drive <= kFastLine, st);
 }
 
 // Euler steps of a full launch of the plan's stepping kernel.
@@ -888,9 +923,8 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
     p->mt_first.push_back((int32_t)p->mt_s.size());
   }
   p->padded = o;
-  double drive = 0.0;  // of a site
-  for (int32_t s = 0; s < p->S; ++s) drive += std::fabs(p->f[s]) * ((double)p->L[s] / (double)p->total_sites);
-  p->fast = drive * p->dt > kFastLine;
+  for (int32_t s = 0; s < p->S; ++s)
+    p->drive += std::fabs(p->f[s]) * p->dt * ((double)p->L[s] / (double)p->total_sites);
   int32_t most = 0;  // measurement tiles of the longest chain
   for (int32_t s = 0; s < p->S; ++s) most = std::max(most, p->mt_first[s + 1] - p->mt_first[s]);
   p->meas_groups = most > kFinalTiles ? 0 : most;

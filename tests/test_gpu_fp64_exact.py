@@ -37,19 +37,30 @@ def _same(qew, p, start=None, tile=0):
 
 
 @pytest.mark.parametrize("kind", [0, 1, 2, 3])
-@pytest.mark.parametrize("f", [20.0, -20.0, 7.0])
-def test_bursts_on_wide_tiles(kind, f):
-    """More cell changes in a wave and step than its request region holds, over a
-    full launch and a part of one, on the widest tiles of every kind."""
+@pytest.mark.parametrize("f,rough,strength", [(1.0, 4.0, 0.7), (-1.0, 8.0, 1.0), (2.0, 0.5, 1.0)])
+def test_bursts_on_wide_tiles(kind, f, rough, strength):
+    """More cell changes in a wave and step than its request region holds, jumps among
+    them, over a full launch and a part of one, on the widest tiles of every kind."""
     from paper_1211_7275_amd import qew
     L = 2_500_001
     print("[gpu-test] FP64 bursts on wide tiles, kind", kind, "f", f, flush=True)
-    start = [np.cumsum(np.random.default_rng(kind).normal(0.0, 0.5, L))]
-    _same(qew, workloads.custom(kind, [L], f, 90, [0], SEED, strength=0.7), start, tile=1024 if kind == 1 else 1536)
+    start = [np.cumsum(np.random.default_rng(kind).normal(0.0, rough, L))]
+    _same(qew, workloads.custom(kind, [L], f, 90, [0], SEED, strength=strength), start, tile=1024 if kind == 1 else 1536)
 
 
 @pytest.mark.parametrize("kind", [0, 1, 2, 3])
-@pytest.mark.parametrize("L", [203, 40_007, 2_500_001])
+@pytest.mark.parametrize("f", [20.0, -20.0, 18.9, 7.0])
+@pytest.mark.parametrize("L", [203, 9001, 40_007])
+def test_every_site_moves_on_narrow_tiles(kind, f, L):
+    """A third of a cell to more than one per step, both directions."""
+    from paper_1211_7275_amd import qew
+    print("[gpu-test] FP64 fast lines, kind", kind, "f", f, "L", L, flush=True)
+    start = [np.cumsum(np.random.default_rng(L + kind).normal(0.0, 0.5, L))]
+    _same(qew, workloads.custom(kind, [L], f, 240, [0], SEED + 2, strength=0.7), start)
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+@pytest.mark.parametrize("L", [203, 40_007])
 @pytest.mark.parametrize("side", [1.0, -1.0])
 def test_last_cells(kind, L, side):
     """Lines that reach the last 32-bit cells, whose windows go on past the largest

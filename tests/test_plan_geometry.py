@@ -79,3 +79,18 @@ def test_fp64_tiles_stay_within_one_launch():
     assert _info([1 << 30] * 13, 1).fp64_tile == 1024
     info = _info([1 << 30] * 15, 1)
     assert info.fp64_tile == 0 and info.n_tiles == 15 * (1 << 30) // 4096
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+def test_fp64_geometry_of_fast_lines(kind):
+    """Lines that move a cell or more in every step remake every window in every step:
+    large batches of them run one step per launch, as do short chains that would take
+    wide tiles, while a few short lines stay on narrow ones."""
+    wide = 1024 if kind == 1 else 1536
+    for f in (20.0, -45.0):
+        assert _info([1 << 22] * 4, kind, f).fp64_tile == 0
+        assert _info([384] * 4096, kind, f).fp64_tile == 0
+        assert _info([1 << 10] * 4, kind, f).fp64_tile == 256
+    assert _info([1 << 22] * 4, kind, 3.0).fp64_tile == wide or kind == 0
+    for f in (5.0, 10.0):
+        assert _info([384] * 4096, kind, f).fp64_tile != wide

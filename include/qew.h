@@ -116,7 +116,10 @@ typedef struct qew_problem {
   int32_t         precision;    /* QEW_FP64_PLAIN or QEW_FP32_SPLIT                     */
   int32_t         path;         /* QEW_ONE_STEP, or QEW_FUSED (FP32 split only)         */
   int32_t         k;            /* fused: steps per launch, 1..128 (0 = autotune)       */
-  int32_t         tile;         /* fused: sites per workgroup tile, 1024/1536/2048/3072/4096 (0 = autotune); 4k <= tile */
+  int32_t         tile;         /* fused: sites per workgroup tile, 1024/1536/2048/3072/4096 (0 = autotune); 4k <= tile;
+                                   or, with k and no variant flag, a narrow geometry as the info of an
+                                   autotuned plan gives it: 256 with k = 112, 96 or 64, and for the
+                                   first two kinds 512 with k = 64 */
   int32_t         flags;        /* QEW_FLAG_* bits                                      */
   int32_t         period;       /* transverse period M of the disorder in u (node n is
                                    node n mod M); 0 = no period; else 1 <= M < 2^30     */

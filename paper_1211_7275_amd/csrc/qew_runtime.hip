@@ -180,6 +180,18 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
   if (p->lay.total) refresh_table_image(p);
 }
 
+// The narrow geometries; the 512-site one is built for the spline kinds only.
+constexpr struct { int tile, k; } kNarrow[4] = {{256, 112}, {256, 96}, {256, 64}, {512, 64}};
+
+// Whether a problem that fixes k and the tile names one of them (as the plan info of
+// another plan gave it).
+bool names_narrow(const qew_problem* pr) {
+  if (pr->path != QEW_FUSED || (pr->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
+  for (const auto& g : kNarrow)
+    if (pr->tile == g.tile && pr->k == g.k) return g.tile == 256 || pr->kind < 2;
+  return false;
+}
+
 bool negative_drive(const qew_plan_t* p) { return *std::min_element(p->f.begin(), p->f.end()) < 0.0; }
 
 // Narrow-tile geometry of the fused path (k_lanes), for small problems where
@@ -200,12 +212,11 @@ bool negative_drive(const qew_plan_t* p) { return *std::min_element(p->f.begin()
 bool narrow_geometry(const qew_plan_t* p, int* tile, int* k) {
   if (!fused(p) || p->k_req || p->tile_req || (p->flags & (QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))) return false;
   const bool hops = p->kind >= 2 || negative_drive(p);
-  struct { int tile, k; int64_t most; } const geometry[] = {
-      {256, 112, 256}, {256, 96, 256}, {256, 64, hops ? 256 : 1024}, {512, 64, hops ? 0 : 1152}};
-  for (const auto& g : geometry) {
-    if (fused_tile_count(p, g.tile, g.k) > g.most) continue;
-    *tile = g.tile;
-    *k = g.k;
+  const int64_t most[4] = {256, 256, hops ? 256 : 1024, hops ? 0 : 1152};
+  for (int i = 0; i < 4; ++i) {
+    if (fused_tile_count(p, kNarrow[i].tile, kNarrow[i].k) > most[i]) continue;
+    *tile = kNarrow[i].tile;
+    *k = kNarrow[i].k;
     return true;
   }
   return false;
@@ -846,10 +857,11 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
   if (pr->path == QEW_FUSED && pr->precision != QEW_FP32_SPLIT)
     return fail(QEW_EUNSUPPORTED, "the fused path runs in FP32 split precision only");
   if (pr->k < 0 || pr->k > kMaxHalo) return fail(QEW_EINVAL, "k must be in [0, %d]", kMaxHalo);
-  if (pr->tile != 0 && pr->tile != 1024 && pr->tile != 1536 && pr->tile != 2048 && pr->tile != 3072 &&
+  const bool narrow = names_narrow(pr);
+  if (!narrow && pr->tile != 0 && pr->tile != 1024 && pr->tile != 1536 && pr->tile != 2048 && pr->tile != 3072 &&
       pr->tile != 4096)
-    return fail(QEW_EINVAL, "tile must be 0, 1024, 1536, 2048, 3072 or 4096");
-  if (pr->k > 0 && pr->tile > 0 && 4 * pr->k > pr->tile) return fail(QEW_EINVAL, "need 4*k <= tile");
+    return fail(QEW_EINVAL, "tile must be 0, 1024, 1536, 2048, 3072 or 4096, or with k a narrow geometry of an autotuned plan");
+  if (!narrow && pr->k > 0 && pr->tile > 0 && 4 * pr->k > pr->tile) return fail(QEW_EINVAL, "need 4*k <= tile");
   if (pr->flags & ~(QEW_FLAG_NO_GRAPH | QEW_FLAG_TIMING | QEW_FLAG_FUSED_DENSE | QEW_FLAG_FUSED_SPARSE))
     return fail(QEW_EINVAL, "unknown flag bits");
   if ((pr->flags & QEW_FLAG_FUSED_DENSE) && (pr->flags & QEW_FLAG_FUSED_SPARSE))
@@ -950,14 +962,14 @@ qew_status qew_plan(const qew_problem* pr, qew_plan_t** out) {
       delete p;
       return fail(QEW_EINVAL, "no fused geometry satisfies 4*k <= tile");
     }
-    if (cap > INT32_MAX / 2) {
+    if (cap > (narrow ? kMaxTiles : INT32_MAX / 2)) {  // narrow: one workgroup per tile
       delete p;
       return fail(QEW_EINVAL, "too many fused tiles");
     }
     p->ft_capacity = (int32_t)cap;
     const int tile0 = p->tile_req ? p->tile_req : 2048;
     int k0 = p->k_req ? p->k_req : 16;
-    if (4 * k0 > tile0) k0 = tile0 / 4;
+    if (!narrow && 4 * k0 > tile0) k0 = tile0 / 4;
     build_fused_tiles(p, tile0, k0);
   } else {
     p->k = 1;

@@ -94,3 +94,25 @@ def test_fp64_geometry_of_fast_lines(kind):
     assert _info([1 << 22] * 4, kind, 3.0).fp64_tile == wide or kind == 0
     for f in (5.0, 10.0):
         assert _info([384] * 4096, kind, f).fp64_tile != wide
+
+
+def test_narrow_geometries_can_be_given():
+    """The (k, tile) pairs that small fused plans are autotuned to, and no others."""
+    def status(kind=0, **options):
+        try:
+            return _info([1000, 64], kind, fp64=False, **options)
+        except qew.QewError as e:
+            assert e.status == qew.QEW_EINVAL
+            return None
+    for k, tile in ((112, 256), (96, 256), (64, 256), (64, 512)):
+        for kind in range(4):
+            info = status(kind, k=k, tile=tile)
+            assert (info is None) == (tile == 512 and kind >= 2)
+            if info:
+                assert (info.k, info.tile, info.autotuned) == (k, tile, 0)
+                assert info.n_tiles == -(-1000 // (tile - 2 * k)) + -(-64 // (tile - 2 * k))
+        assert status(k=k, tile=tile, flags=qew.QEW_FLAG_FUSED_DENSE) is None
+        assert status(k=k, tile=tile, flags=qew.QEW_FLAG_FUSED_SPARSE) is None
+        assert status(k=k, tile=tile, path=qew.QEW_ONE_STEP) is None
+    for k, tile in ((0, 256), (0, 512), (32, 256), (65, 256), (112, 512), (128, 256), (64, 768)):
+        assert status(k=k, tile=tile) is None

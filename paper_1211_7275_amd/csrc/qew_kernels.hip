@@ -1625,26 +1625,31 @@ hipError_t launch_step_plain(const Tables& t, const double* uin, double* uout, c
   return hipGetLastError();
 }
 
+// False: no kernel of this tile.
 template <int KIND>
-static void launch_blocked_kind(const Tables& t, const double* uin, double* uout, const Phys& ph, int tile,
+static bool launch_blocked_kind(const Tables& t, const double* uin, double* uout, const Phys& ph, int tile,
                                 int halo, int nsub, hipStream_t st) {
   const dim3 g(t.n_ft), b(kBlock);
   constexpr int wide = blocked_wide_tile(KIND) / kBlock;
   if (tile == wide * kBlock) hipLaunchKernelGGL((k_blocked_plain<KIND, wide>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
   else if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 1>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
-  else if constexpr (KIND < kRBLin)  // 512, which the rule takes for the spline kinds only
-    hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  else if (KIND < kRBLin && tile == 512) {
+    if constexpr (KIND < kRBLin)
+      hipLaunchKernelGGL((k_lanes<LanesD<KIND>, 2>), g, b, 0, st, t, uin, uout, ph, halo, nsub);
+  } else return false;
+  return true;
 }
 
 hipError_t launch_blocked_plain(const Tables& t, const double* uin, double* uout, const Phys& ph, int kind,
                                 int tile, int halo, int nsub, hipStream_t st) {
+  bool ok = false;
   switch (kind) {
-    case kRF: launch_blocked_kind<kRF>(t, uin, uout, ph, tile, halo, nsub, st); break;
-    case kRB: launch_blocked_kind<kRB>(t, uin, uout, ph, tile, halo, nsub, st); break;
-    case kRBLin: launch_blocked_kind<kRBLin>(t, uin, uout, ph, tile, halo, nsub, st); break;
-    default: launch_blocked_kind<kRFPc>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    case kRF: ok = launch_blocked_kind<kRF>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    case kRB: ok = launch_blocked_kind<kRB>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    case kRBLin: ok = launch_blocked_kind<kRBLin>(t, uin, uout, ph, tile, halo, nsub, st); break;
+    default: ok = launch_blocked_kind<kRFPc>(t, uin, uout, ph, tile, halo, nsub, st); break;
   }
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <int KIND>
@@ -1726,42 +1731,45 @@ struct FusedLaunch {
   }
 };
 
+// False: no kernel of this tile and variant.
 template <int KIND, bool SPARSE>
-static void launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int tile,
+static bool launch_fused_kind(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int tile,
                               int halo, int nsub, bool rounds, dim3 g, dim3 b, hipStream_t st) {
-  if constexpr (!SPARSE) {
-    if (tile == 256 || tile == 512) {  // one workgroup per tile
-      if (tile == 256) hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 1>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
-      else if constexpr (KIND < kRBLin)  // 512, which the rule takes for the spline kinds only
-        hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 2>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
-      return;
-    }
-  }
   const FusedLaunch l{t, in, out, ph, halo, nsub, rounds, g, b, st};
-  if (tile == 1024) l.template run<KIND, 4, SPARSE>();
-  else if (tile == 1536) l.template run<KIND, 6, SPARSE>();
-  else if (tile == 2048) l.template run<KIND, 8, SPARSE>();
-  else if (tile == 3072) l.template run<KIND, 12, SPARSE>();
-  else l.template run<KIND, 16, SPARSE>();
+  switch (tile) {
+    case 256:  // narrow tiles: one workgroup per tile, no sparse variant
+      if constexpr (!SPARSE) hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 1>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
+      return !SPARSE;
+    case 512:  // for the spline kinds
+      if constexpr (!SPARSE && KIND < kRBLin)
+        hipLaunchKernelGGL((k_lanes<LanesS<KIND>, 2>), dim3(t.n_ft), b, 0, st, t, in, out, ph, halo, nsub);
+      return !SPARSE && KIND < kRBLin;
+    case 1024: l.template run<KIND, 4, SPARSE>(); return true;
+    case 1536: l.template run<KIND, 6, SPARSE>(); return true;
+    case 2048: l.template run<KIND, 8, SPARSE>(); return true;
+    case 3072: l.template run<KIND, 12, SPARSE>(); return true;
+    case 4096: l.template run<KIND, 16, SPARSE>(); return true;
+    default: return false;
+  }
 }
 
 template <bool SPARSE>
-static void launch_fused_variant(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
+static bool launch_fused_variant(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
                                  int tile, int halo, int nsub, bool rounds, dim3 g, dim3 b, hipStream_t st) {
   switch (kind) {
-    case kRF: launch_fused_kind<kRF, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
-    case kRB: launch_fused_kind<kRB, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
-    case kRBLin: launch_fused_kind<kRBLin, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
-    default: launch_fused_kind<kRFPc, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st); break;
+    case kRF: return launch_fused_kind<kRF, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st);
+    case kRB: return launch_fused_kind<kRB, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st);
+    case kRBLin: return launch_fused_kind<kRBLin, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st);
+    default: return launch_fused_kind<kRFPc, SPARSE>(t, in, out, ph, tile, halo, nsub, rounds, g, b, st);
   }
 }
 
 hipError_t launch_step_fused(const Tables& t, SplitBuf in, SplitBuf out, const Phys& ph, int kind,
                              int tile, int halo, int nsub, int grid, bool sparse, bool rounds, hipStream_t st) {
   const dim3 g(grid), b(kBlock);
-  if (sparse) launch_fused_variant<true>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st);
-  else launch_fused_variant<false>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st);
-  return hipGetLastError();
+  const bool ok = sparse ? launch_fused_variant<true>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st)
+                         : launch_fused_variant<false>(t, in, out, ph, kind, tile, halo, nsub, rounds, g, b, st);
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <int KIND>

@@ -387,8 +387,10 @@ void compute_layout(qew_plan_t* p) {
     const size_t half = (size_t)(p->L[0] / 2);
     l.sq_series = take(std::max<size_t>(p->meas.size(), 1) * p->sq_bins * 8);
     l.sq_part = take(p->sq_chunk_lo.size() * 8);
-    l.fftA = take(S * half * 16 + (half + 1) * 8);  // either buffer may hold S_n and the mean
-    l.fftB = take(S * half * 16 + (half + 1) * 8);  // also holds the per-mode mean
+    // Either also holds the sums over groups of samples, G <= S rows of half + 1, and
+    // with more than four of them a row for the mean: (S + 1) (half + 1) <= 2 S half there.
+    l.fftA = take(S * half * 16);
+    l.fftB = take(S * half * 16);
   } else {
     l.sq_series = l.sq_part = l.fftA = l.fftB = 0;
   }

@@ -556,7 +556,7 @@ hipError_t launch_sq(const int64_t* off, int S, int64_t L, const double* u_plain
   }
   int samples = S;
   if (G > 4) {  // many rows: one thread per mode adds them first
-    double* mean = rows + (int64_t)G * (N + 1);  // fits behind the rows: a buffer holds S N + (N + 1) / 2 points
+    double* mean = rows + (int64_t)G * (N + 1);  // fits behind the rows: (G + 1) (N + 1) <= 2 S N
     hipLaunchKernelGGL(k_sq_mean, dim3((unsigned)(N / 64 + 1)), dim3(64), 0, st, rows, mean, N, G, S);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     rows = mean;

@@ -302,7 +302,7 @@ constexpr double kLaunchCost = 4.0;  // us per launch: the gap, the tiles' loads
 // 0.8): linear random bond 256/64 at 2^13 1.84, at 2^14 2.87, against 2.84 wide;
 // without interpolation at 2^14 1.98 (256/64) against 2.4 wide.
 void build_blocked_tiles(qew_plan_t* p) {
-  if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0) return;
+  if (p->precision != QEW_FP64_PLAIN || p->strength == 0.0 || p->k_req == 1) return;
   const BlockedCost& cost = blocked_cost(p);
   const OneStepCost& one = kOneStepCost[p->kind];
   const struct { int tile, k; const TileCost& c; } geometry[] = {{256, 112, cost.t256},

@@ -98,3 +98,19 @@ def test_last_cells_split(kind, L, k, tile):
             sim.close()
     assert got[0].max() < 0.0  # past the last cell
     assert np.array_equal(got[0], got[1])
+
+
+def test_one_step_per_launch_on_request():
+    """k = 1: as many launches as steps, replayed as graphs, and the chosen path's bits."""
+    from paper_1211_7275_amd import qew
+    p = workloads.custom(0, [5000, 40_007], 1.2, 300, [0, 50], SEED + 3)
+    runs = []
+    for k in (0, 1):
+        with qew.Simulation(p, precision=qew.QEW_FP64_PLAIN, path=qew.QEW_ONE_STEP, k=k) as sim:
+            out = sim.run()
+            st = sim.stats()
+            assert st.step_launches == 300 if k else st.step_launches < 30
+            assert st.graph_launches > 0 or not k
+            runs.append([out["v"], out["w2"], out["ubar"]] + [sim.read_state(s)[0] for s in range(2)])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)

@@ -36,6 +36,8 @@ def test_plans_of_one_step_per_launch_report_none():
                  _info([1 << 16] * 4, fp64=False, k=32, tile=2048)):
         assert info.fp64_k == 0 and info.fp64_tile == 0
     assert _info([1 << 16] * 4, strength=0.0).n_tiles == 64
+    one = _info([1 << 16] * 4, k=1)  # asked for
+    assert one.fp64_k == 0 and one.fp64_tile == 0 and one.n_tiles == 64
 
 
 @pytest.mark.parametrize("chains", [512, 4096, 32768])

@@ -162,11 +162,11 @@ bool lanes(const qew_plan_t* p) { return fused(p) && p->tile < 1024; }
 void refresh_table_image(qew_plan_t* p);
 int64_t fused_tile_count(const qew_plan_t* p, int tile, int k);
 
-void build_fused_tiles(qew_plan_t* p, int tile, int k) {
+// The tiles of V valid sites of every chain, in order.
+void list_tiles(qew_plan_t* p, int64_t V) {
   p->ft_s.clear();
   p->ft_p0.clear();
   p->ft_len.clear();
-  const int64_t V = tile - 2 * k;
   for (int32_t s = 0; s < p->S; ++s) {
     const int64_t L = p->L[s];
     for (int64_t p0 = 0; p0 < L; p0 += V) {
@@ -175,6 +175,10 @@ void build_fused_tiles(qew_plan_t* p, int tile, int k) {
       p->ft_len.push_back((int32_t)std::min<int64_t>(V, L - p0));
     }
   }
+}
+
+void build_fused_tiles(qew_plan_t* p, int tile, int k) {
+  list_tiles(p, tile - 2 * k);
   p->k = k;
   p->tile = tile;
   if (p->lay.total) refresh_table_image(p);
@@ -325,19 +329,7 @@ void build_blocked_tiles(qew_plan_t* p) {
     p->btile = g.tile;
     p->bk = g.k;
   }
-  if (p->bk == 0) return;
-  const int64_t V = p->btile - 2 * p->bk;
-  p->ft_s.clear();
-  p->ft_p0.clear();
-  p->ft_len.clear();
-  for (int32_t s = 0; s < p->S; ++s) {
-    const int64_t L = p->L[s];
-    for (int64_t p0 = 0; p0 < L; p0 += V) {
-      p->ft_s.push_back(s);
-      p->ft_p0.push_back((int32_t)p0);
-      p->ft_len.push_back((int32_t)std::min<int64_t>(V, L - p0));
-    }
-  }
+  if (p->bk) list_tiles(p, p->btile - 2 * p->bk);
 }
 
 int64_t fused_tile_count(const qew_plan_t* p, int tile, int k) {

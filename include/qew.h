@@ -21,6 +21,8 @@
  *     Values are scaled by `strength`.  Generator: Philox4x32-10 (Salmon et
  *     al., SC'11) with counter (j, (uint32) n, disorder_id, 0) and key
  *     (seed low word, seed high word).
+ *     Cells are 32-bit integers; a line that leaves (-2^31, 2^31) is beyond
+ *     the range that results are defined for.
  *   - Observables of Sec. II, Eqs. (3)-(5), per sample s at every requested
  *     measurement step m: v_s(m) = mean over j of the total force at step m
  *     (equal to the mean of du/dt), ubar_s(m) = mean of u_j, and
@@ -69,7 +71,8 @@ typedef int32_t qew_status;
 /* kernel path */
 #define QEW_ONE_STEP 0        /* split: one Euler step per launch, all 4 nodes regenerated;
                                  FP64: up to 112 steps per launch on overlapping tiles
-                                 (geometry from the problem's size), the same results    */
+                                 (geometry from the problem's sizes and drives), the same
+                                 results as one step per launch (k = 1)                  */
 #define QEW_FUSED    1        /* k Euler steps per launch on register tiles with halos */
 
 /* qew_problem.flags */
@@ -190,8 +193,9 @@ qew_status qew_plan_info_get(const qew_plan_t *plan, qew_plan_info *info);
  * Choose k and the tile width of the fused path by timing short runs on the
  * workspace (its state is overwritten).  Where the problem left both open and
  * is small, narrow tiles (256 or 512 sites, up to 112 steps per launch) are
- * taken by a rule on the number of tiles instead, unless a flag forces a variant.  Called by qew_run by itself when the
- * problem left k or tile at 0.  No-op for the one-step path.
+ * taken by a rule on the number of tiles instead, unless a flag forces a
+ * variant.  Called by qew_run by itself when the problem left k or tile at 0.
+ * No-op for the one-step path.
  */
 qew_status qew_autotune(qew_plan_t *plan, void *d_ws, size_t ws_bytes, void *stream);
 
@@ -214,8 +218,8 @@ qew_status qew_run(qew_plan_t *plan, void *d_ws, size_t ws_bytes, void *stream, 
  * harnesses that forbid allocation): the same arguments, kernels and results
  * as qew_run, but the call allocates nothing, on the device or the host.  Like
  * qew_run it synchronizes its stream (the tables go in and the series come out
- * by copies), so the call itself cannot be recorded into a HIP graph.  The chains stay in d_ws (its size and
- * alignment as for qew_run); the plan's tables, tile lists, measurement
+ * by copies), so the call itself cannot be recorded into a HIP graph.  The chains
+ * stay in d_ws (its size and alignment as for qew_run); the plan's tables, tile lists, measurement
  * partials and series live in a device scratch array of the library, 8 MiB
  * per GPU, held from the library's load until the process ends (its address
  * is looked up once per device, on the first call there).  No autotuning,

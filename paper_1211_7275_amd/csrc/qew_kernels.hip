@@ -8,10 +8,11 @@
 //   k_step_plain   one FP64 Euler step per launch, one thread per site, four
 //                  Philox nodes regenerated per site update.  HBM traffic is
 //                  16 B per update (read u, write u; neighbours hit L1/L2).
-//   k_blocked_plain, k_lanes
+//   k_blocked_plain
 //                  several FP64 steps per launch on overlapping tiles, nodes
-//                  made when a site enters a cell: wide tiles for large
-//                  problems, narrow ones without a request path for small.
+//                  made when a site enters a cell.
+//   k_lanes        the same in both precisions for small problems: narrow tiles,
+//                  every lane makes its own nodes, no request path.
 //   k_step_split1  the same on the split state (int32 cell + FP32 offset).
 //   k_step_fused   `nsub` split Euler steps per launch.  Each workgroup owns
 //                  a tile of 256*P consecutive sites held in registers (P
@@ -888,7 +889,8 @@ __device__ __forceinline__ double from_upper_lane(double x) {
 
 // Waves per SIMD the register allocation must allow.  Random bond: no more fit
 // the LDS.  Linear random bond: the Box-Muller transform and its windows spill
-// at four (107 us per step at 2^22 x 4 against 63).
+// at four (107 us per step at 2^22 x 4 against 63).  The other two spill 3 and 6
+// registers at four, and run faster than at three all the same (see above).
 constexpr int blocked_min_waves(int kind) { return kind == kRF || kind == kRFPc ? 4 : 3; }
 
 template <int KIND, int P>
@@ -1114,7 +1116,7 @@ __global__ void __launch_bounds__(kBlock, blocked_min_waves(KIND))
 
 // ---------------------------------------------------------------------------
 // Temporally blocked kernel for small problems, both precisions: nsub <= halo
-// Euler steps per launch on tiles of 256 P sites with P = 1, 2 or 4.
+// Euler steps per launch on tiles of 256 P sites with P = 1 or 2.
 //
 // When there are only a few sites per CU, a sub-step costs what its longest
 // dependent chain costs.  The request path of the wide-tile kernels (post in
@@ -1351,7 +1353,11 @@ __global__ void __launch_bounds__(kBlock, P == 1 ? 4 : 3)
         next[i] = s_ahead[node_after(A::cell(x[i], cbase), A::kHigh + 1) & (kSpare - 1)][i * kBlock + tid];
       }
       const bool other = d[i] != 0 && !up;
-      if (__ballot(other) != 0u) {  // rare: backwards, or more than one cell
+      // Backwards, or more than one cell: the whole window.  Rare on lines that
+      // move forward; the main path of the kinds whose force jumps, whose sites hop
+      // between two cells, and of lines under a negative drive, for which the rules
+      // of the geometry therefore end the narrow tiles early.
+      if (__ballot(other) != 0u) {
         if (other) {
           fresh(x[i], col[i]);
           A::coef(x[i], k);
